@@ -106,8 +106,9 @@ typedef enum {
  *                     1 MB (p <= 96) or 512 KB,
  *                     for calls that run in subtree work items (p >= 256
  *                     and at most two such items per CU, at least one per
- *                     four CUs; from p = 4096 on, calls of three or four
- *                     per CU run them split), and for calls that run in
+ *                     four CUs) and move at most 256 MB (on rows off the
+ *                     128-byte lines only in pieces of at least 512 bytes;
+ *                     other such calls run split), and for calls that run in
  *                     wide work items
  *                     with p <= 36 and at most one such item (16 KB of
  *                     columns) per CU, with p <= 20 and at most two, or
@@ -359,11 +360,13 @@ const char* dpar_last_error(void);
  *                           every wide call, also the fused calls of at
  *                           most 20 ranks that otherwise take full items
  *                           only; tests)
- *   DPAR_LEVEL_LOG2T=k      level work items of 2^k quanta (at most what
- *                           fits in LDS)
- *   DPAR_SUB_DEEP=0|1       subtree work items with 8 or 16 loads in flight
- *                           per wavefront (default 16 from p = 1024 on when
- *                           the call has at most one item per CU)
+ *   DPAR_LEVEL_LOG2T=k      level work items (and the subtree items of SPLIT
+ *                           and of fused launches) of 2^k quanta (at most
+ *                           what fits in LDS)
+ *   DPAR_SUB_DEEP=0|1       subtree work items of the other executors, or
+ *                           forced by DPAR_UNIT=sub, with 8 or 16 loads in
+ *                           flight per wavefront (default 16 from p = 1024
+ *                           on when the call has at most one item per CU)
  *   DPAR_WAVES=1|2          wavefronts per post-order work item (default
  *                           1 for p <= 48, else 2)
  *   DPAR_TICKET_BATCH=k     work items claimed per ticket (TICKET)
@@ -385,9 +388,10 @@ const char* dpar_last_error(void);
  *                           resident per CU (default 4; 0 = as many as
  *                           fit); set, it applies to every SPLIT call with
  *                           post-order work items
- *   DPAR_XCD_RUNS=0|1       SPLIT's up-phase: each XCD takes a contiguous
- *                           run of work items (default 1 only when some
- *                           input row is off a 128-byte line)
+ *   DPAR_XCD_RUNS=0|1       SPLIT's up-phase, fused level and subtree items:
+ *                           each XCD takes a contiguous run of work items
+ *                           (default 1 only when some input row, or output
+ *                           row of a fused launch, is off a 128-byte line)
  *   DPAR_BCAST_FASTDIV=0|1  SPLIT's broadcast pass: workgroups find their
  *                           row and tile by multiplication (1; default for
  *                           passes writing at most 2 GB) or by division (0)

@@ -72,9 +72,31 @@ constexpr int kWideLateRanks = 16;
 constexpr int kLvSplitRanks = 1024;
 constexpr int kLvSplitManyRanks = 512;
 constexpr int kLvCrowdRanks = 2048;
+// Bytes of each row a level item reads at least (kLvMinPieceDeep from
+// kLvCrowdRanks ranks on): int32 SUM, p = 1152, m = 1024 (256 quanta) fused
+// with 32 / 64 / 128 / 256 bytes 11.0 / 9.7 / 11.1 / 16.0 us, p = 288,
+// m = 875 with 16 / 32 / 64 / 128 bytes 7.1 / 6.6 / 6.6 / 8.1 us; p = 2304,
+// m = 4096 with 64 / 128 bytes 27.5 / 22.0 us.
+constexpr size_t kLvMinPiece = 64;
+constexpr size_t kLvMinPieceDeep = 128;
+// From this many ranks (up to 255) level items take one-launch calls of up to
+// one 1 KB chunk of each row per CU (post-order -> level, one fused launch:
+// p = 36, m = 65536 8.9 -> 6.1 us, p = 64 9.5 -> 7.6 us, p = 128 17.0 ->
+// 12.8 us, p = 200 26.2 -> 18.1 us; with two chunks per CU p = 64 13.5 ->
+// 14.7 us, p = 128 25.1 -> 25.3 us; at p = 16 within 0.6 us either way).
+constexpr int kLvMinRanks = 17;
+// AUTO: subtree items run fused in calls moving at most this much (p = 300,
+// m = 100000, 240 MB: fused 41 us, split 44 us; p = 576, m = 65536, 302 MB:
+// 52 and 50 us; p = 1152, m = 65536, 604 MB: 108 and 96 us), and on rows off
+// the 128-byte lines only with pieces of at least kSubFuseMinPiece bytes,
+// whose ends then share lines with other items' (packed rows: p = 600,
+// m = 20001, 512 bytes: fused 28.0 us, split 30.6 us; p = 1152, m = 16385,
+// 256 bytes: 57 and 42 us).
+constexpr uint64_t kSubFuseMaxBytes = 256ull << 20;
+constexpr size_t kSubFuseMinPiece = 512;
 // Ranks from which subtree items take calls of up to four items per CU.
 constexpr int kSubCrowdRanks = 4096;
-// Level work item: loads in flight at once (1024 threads, 8 loads each).
+// Loads in flight of a workgroup of 1024 threads with 8 each.
 constexpr uint64_t kLvLoadsInFlight = 1024 * 8;
 // Ticket executor: rank loads per claimed batch of work items.
 constexpr uint64_t kTicketRankLoads = 1024;
@@ -100,9 +122,19 @@ constexpr int kBcastSpanKB = 16384;
 // faster one (2.65 against 2.73 ms).
 constexpr uint64_t kBcastFastDivMaxBytes = 2ull << 30;
 
+// A group plan's counts (plan.hpp GroupPlan).
+struct GroupInts {
+  int g1 = 0, g2 = 0, nst = 1, val_a = 0, val_b = 0, extra = -1;
+  GroupInts() = default;
+  explicit GroupInts(const dpar::GroupPlan& g)
+      : g1(g.g1), g2(g.g2), nst(g.nst), val_a(g.val_a), val_b(g.val_b),
+        extra(g.extra) {}
+};
+
 struct OpsTable {
   uint32_t* dev = nullptr;   // opcodes, padded
-  uint32_t* lvl = nullptr;   // level-ordered entries + boundaries (p <= 65534)
+  uint32_t* lvl = nullptr;   // group table of the level item (p <= 65534)
+  GroupInts lv;              // its counts
   uint32_t* dn = nullptr;    // parent << 8 | depth of the real tree(s)
   uint32_t* dord = nullptr;  // depth offsets + non-root ranks by depth
   uint32_t* sub = nullptr;   // subtree work-item plan (null: not available)
@@ -270,8 +302,11 @@ int get_ops(DeviceState* st, int p, bool single, const OpsTable** out) {
     rc = upload(sub, &tab.sub, "subtree plan");
     tab.sub_ns = (int)sub[3];
   }
-  if (!rc && p <= 65534) rc = upload(dpar::make_levels(kt), &tab.lvl,
-                                     "level table");
+  if (!rc && p <= 65534) {
+    const dpar::GroupPlan g = dpar::make_groups(kt);
+    if (g.ok) rc = upload(dpar::group_table(g), &tab.lvl, "group table");
+    tab.lv = GroupInts(g);
+  }
   if (!rc && p < (1 << 24) && real.height < 256) {
     rc = upload(dpar::make_down(real), &tab.dn, "parent table");
     const std::vector<uint32_t> dord = dpar::make_depth_order(real);
@@ -507,7 +542,8 @@ int fixed_tables(FixedState* f, int p, hipStream_t stream,
   std::vector<uint32_t> sub;
   const bool has_sub = p >= 64 && dpar::make_sub(kt, ops, 2, &sub);
   ops.resize(ops.size() + dpar::kTablePad, 0u);  // kernels read ahead
-  const std::vector<uint32_t> lvl = dpar::make_levels(kt);
+  const dpar::GroupPlan groups = dpar::make_groups(kt);
+  const std::vector<uint32_t> lvl = dpar::group_table(groups);
   const size_t off_lvl = align256(ops.size() * 4);
   const size_t off_sub = off_lvl + align256(lvl.size() * 4);
   const size_t off_ptr = off_sub + align256(sub.size() * 4);
@@ -527,6 +563,7 @@ int fixed_tables(FixedState* f, int p, hipStream_t stream,
   OpsTable t;
   t.dev = reinterpret_cast<uint32_t*>(base);
   t.lvl = reinterpret_cast<uint32_t*>(base + off_lvl);
+  t.lv = GroupInts(groups);
   t.sub = has_sub ? reinterpret_cast<uint32_t*>(base + off_sub) : nullptr;
   t.sub_ns = has_sub ? (int)sub[3] : 0;
   t.height = kt.height;
@@ -856,19 +893,42 @@ uint64_t wide_full_items(uint64_t n, const DeviceState& st) {
 
 struct UnitChoice {
   dpar::Unit unit = dpar::Unit::SEQ;
-  int lv_log2t = 0;  // LEVEL: log2 of the chunk capacity in quanta
-  int lv_C = 1;      // LEVEL: chunks per block
+  bool grouped = false;   // SUB: run as grouped items over whole chunks
+  int lv_log2t = 0;       // LEVEL, grouped: log2 of the chunk in quanta
+  int lv_C = 1;           // LEVEL: chunks per block
+  uint64_t lv_items = 0;  // LEVEL: items if chunks were staged row by row
 };
+
+// Quanta per chunk of a level item, as a power of two: the smallest chunk
+// that leaves at most one item per CU (items(l): how many there are with 2^l
+// quanta), between kLvMinPiece bytes of each row (kLvMinPieceDeep from
+// kLvCrowdRanks ranks on) and what fits in LDS, at most 64.
+// DPAR_LEVEL_LOG2T forces it.
+template <class F>
+int level_log2t(size_t lane_bytes, int p, int g1, const DeviceState& st,
+                F items) {
+  int top = 6;
+  while (top > 0 && dpar::level_lds_bytes(lane_bytes, g1, top) >
+                        (size_t)st.lds_limit - dpar::kStaticLdsReserve)
+    --top;
+  const int forced_lg = env_int("DPAR_LEVEL_LOG2T", -1);
+  if (forced_lg >= 0) return std::min(forced_lg, top);
+  const size_t piece = p >= kLvCrowdRanks ? kLvMinPieceDeep : kLvMinPiece;
+  int lg = 0;
+  while (lg < top && (lane_bytes << lg) < piece) ++lg;
+  while (lg < top && items(lg) > (uint64_t)st.num_cus) ++lg;
+  return lg;
+}
 
 // How work items are evaluated (DPAR_UNIT=seq|level|sub forces one):
 //   SEQ   post-order walk, one wavefront per tree: the default;
-//   LEVEL the chunk staged in LDS, level by level: when the chunks of a round
-//         (per-round executors) or of the whole call number fewer than half
-//         a chunk per CU (measured crossover at p = 1152, m = 2^22: 249
-//         chunks per round 10.1 ms post-order vs 12.8 ms level; 110 chunks
-//         17.9 vs 15.8 ms), or for few short chunks with long chains (a
-//         post-order item costs its p/2-load chain however little it
-//         carries: p = 1152, m = 4096, b = 205: 117 us post-order, 31 level);
+//   LEVEL groups of at most 7 ranks per thread, three tree levels per step
+//         (kernels.hip run_unit_lv): when the chunks of a round (per-round
+//         executors) or of the whole call number fewer than half a chunk per
+//         CU, for few short chunks with long chains (a post-order item costs
+//         its p/2-load chain however little it carries: p = 1152, m = 1024
+//         103 us post-order, 11 level), and with 17 to 255 ranks in one
+//         launch up to a chunk per CU (kLvMinRanks);
 //   WIDE  the post-order walk with kWideQ quanta per lane: a whole call
 //         (split, ticket, one fused launch) on 16-byte lanes whose slots
 //         fit in LDS (p < 1024) with at least 3/4 of a wide item (16 KB
@@ -883,14 +943,17 @@ struct UnitChoice {
 //         under the cap, p = 256 .. 768 with 16 MB rows, post-order items
 //         are 0-4% faster; 2 wavefronts per item for deeper trees won only
 //         at p = 1152 with 4 MB rows and lost up to 30% elsewhere);
-//   SUB   eight subtree walks, then the spines: a whole call (split,
-//         ticket, one fused launch) in at most two full chunks per CU
-//         with p >= 256 (p = 1152, m = 2^16, b = 1: 0.113 vs 0.165 ms;
-//         two per CU, p = 1152, m = 2^17: 0.240 vs 0.260 ms), and in
-//         place of LEVEL at p >= 256 when the level plan needs more than
-//         two items per CU; for launch per round and grid barrier only when
-//         a round has half a chunk to two chunks per CU, none of them short
-//         (elsewhere it loses).
+//   SUB   p >= 256 and a whole call (split, ticket, one fused launch) in at
+//         most two full chunks per CU, or more where the rules below say so,
+//         and in place of LEVEL when a level plan staged row by row would
+//         need more than two items per CU.  Split and fused calls run it as
+//         level items over whole chunks (UnitChoice::grouped; against the
+//         eight subtree walks per item that the other executors, and
+//         DPAR_UNIT=sub, run: p = 1152, m = 16384 fused 44.9 -> 28.4 us,
+//         m = 65536 102 -> 96 us, p = 2304, m = 16384 84 -> 51 us, p = 4608,
+//         m = 16384 164 -> 106 us, p = 300, m = 100000 44 -> 41 us).  Launch
+//         per round and grid barrier take the walks when a round has half a
+//         chunk to two chunks per CU, none of them short.
 UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
                        dpar::Path path, dpar::Kind kind, int p,
                        const OpsTable& ops, const DeviceState& st) {
@@ -907,6 +970,8 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   const bool whole_call = ex == dpar::Exec::SPLIT ||
                           ex == dpar::Exec::TICKET ||
                           ex == dpar::Exec::DISPATCH;
+  // the split executor or one fused launch
+  const bool one_pass = ex == dpar::Exec::SPLIT || ex == dpar::Exec::DISPATCH;
   const size_t lane_bytes =
       (path == dpar::Path::VEC16 || kind == dpar::Kind::MAT) ? 16 : 4;
   // a one-launch subtree run cuts the columns into whole chunks of 64
@@ -929,26 +994,36 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
                          (uint64_t)s.C <= 2 * cus && s.Q >= 32 * all_items;
   // From kSubCrowdRanks ranks on subtree items also take calls of up to
   // four per CU (split; post-order chains of p / 2 loads are then the
-  // longer wait): p = 4608, m = 2^18 (1024 items), median of four runs,
-  // post-order split 1685 us back to back / 2086 us after a cache flush,
-  // subtree split 1528 / 1897 us; at p = 2304 post-order items stay
-  // faster (735 / 884 against 798 / 971 us).
+  // longer wait): p = 4608, m = 131072 842 -> 729 us, m = 2^18 1685 ->
+  // 1500 us; at p = 2304 post-order items stay faster (701 against 725 us).
   const bool sub_crowd = whole_call && p >= kSubCrowdRanks &&
                          sub_items <= 4 * cus;
+  // chunk of a level item that follows no blocks
+  const int flat_lt =
+      ops.lvl ? level_log2t(lane_bytes, p, ops.lv.g1, st,
+                            [&](int l) { return (s.Q + (1ull << l) - 1) >> l; })
+              : 0;
   bool want_sub = p >= 256 && sub_fits &&
                   ((whole_call && sub_items <= 2 * cus) || sub_crowd ||
                    round_sub);
   if (ops.lvl) {
+    // Level or subtree.  In one launch both run the same item and the family
+    // only sets who writes the outputs (the AUTO rules in allreduce_impl);
+    // with the ticket executor subtree items are walks, which are the better
+    // ones when level items would be many and hold little of each row.  The
+    // measure is the chunk that fits when a level item stages its quanta of
+    // all p rows in LDS, with its loads in flight at once, larger only while
+    // such items outnumber the CUs: more than two per CU (four from
+    // kLvCrowdRanks ranks on) are too many, and so is more than one if there
+    // are subtree items for a quarter of the CUs.
     int tmax = -1;
-    for (int lg = 6; lg >= 0; --lg) {
-      if (dpar::level_lds_bytes(path, kind, p, lg, ops.height + 1) <=
-          (size_t)st.lds_limit - dpar::kStaticLdsReserve) {
+    for (int lg = 6; lg >= 0 && tmax < 0; --lg)
+      if ((((uint64_t)p + 1) << lg) * lane_bytes + 12ull * (uint64_t)p + 256 <=
+          (uint64_t)st.lds_limit - dpar::kStaticLdsReserve)
         tmax = lg;
-        break;
-      }
-    }
     bool want = items < cus / 2 ||
-                (p >= 256 && items < 2 * cus && s.Q < 32 * all_items);
+                (p >= 256 && items < 2 * cus && s.Q < 32 * all_items) ||
+                (one_pass && p >= kLvMinRanks && p < 256 && sub_items <= cus);
     if (forced) want = !std::strcmp(u, "level");
     if (want && tmax >= 0) {
       // largest block (group of grp blocks) in quanta; chunk capacity T =
@@ -961,46 +1036,24 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
       auto chunks = [&](int l) { return (maxq + (1ull << l) - 1) >> l; };
       const uint64_t groups =
           per_round ? 1 : ((uint64_t)s.b + (uint64_t)grp - 1) / (uint64_t)grp;
-      // At large p a level item holds only a few quanta of each row; when
-      // that takes more than two level items per CU (four from
-      // kLvCrowdRanks ranks on) and the subtree item can take the call,
-      // it is faster (p = 2304, m = 2^14,
-      // b = 1: 1024 level items 0.200 ms, 64 subtree items 0.116 ms;
-      // p = 4608: 0.494 vs 0.213 ms; p = 1152 keeps level items: 512 of
-      // them, 0.054 vs 0.068 ms; int32 SUM, the rule's b, level items
-      // split: p = 2304, m = 4096, 544 level items 67 us, subtree items
-      // 91 us; m = 8192, 1088 level items 105 us, subtree 95 us; p = 4608,
-      // m = 4096, 1024 level items 149 us, subtree 163 us).
       const uint64_t crowd = p >= kLvCrowdRanks ? 4 : 2;
       const bool crowded = groups * chunks(lg_max) > crowd * cus;
-      // Chunk used: the largest whose p * T loads are all in flight at once
-      // (1024 threads with kLvBatch loads each), larger only while the items
-      // outnumber the CUs.  Measured, int32 SUM, one fused launch: p = 288,
-      // m = 875: T = 64 (the largest that fits) 19.4 us, T = 16 14.5 us;
-      // m = 25: 15.5 vs 14.2 us; p = 1152, m = 16, b = 13: 19.7 vs
-      // 15.3 us; p = 1152, m = 4096: T = 2 (512 items) 41.2 us, T = 4
-      // 20.6 us.
       int lg = 0;
       while (lg < lg_max && ((uint64_t)p << (lg + 1)) <= kLvLoadsInFlight)
         ++lg;
       while (lg < lg_max && groups * chunks(lg) > cus) ++lg;
-      const int forced_lg = env_int("DPAR_LEVEL_LOG2T", -1);
-      if (forced_lg >= 0) lg = std::min(forced_lg, tmax);
-      const int lv_C = (int)chunks(lg);
-      // A level plan of more than one item per CU ends with a round that
-      // is not full, each of its items as long as a whole round's; subtree
-      // items, at least a quarter of one per CU, take such a call faster
-      // (p = 400, m = 16384: 304 level items 31-33 us, 64 subtree items
-      // 27-31 us; m = 24576, p = 350 .. 600: 384 level items 35-49 us,
-      // 96 subtree items 28-45 us); with fewer subtree items their chains
-      // cost more (p = 1152, m = 8192: 264 level items 43-48 us, 32
-      // subtree items 52-55 us).
-      const uint64_t lv_items = groups * (uint64_t)lv_C;
+      const uint64_t lv_items = groups * chunks(lg);
       const bool lv_rounds = lv_items > cus && 4 * sub_items >= cus;
       if (forced || !((crowded || lv_rounds) && want_sub)) {
         uc.unit = dpar::Unit::LEVEL;
-        uc.lv_log2t = lg;
-        uc.lv_C = lv_C;
+        uc.lv_items = lv_items;
+        // the chunk itself
+        uc.lv_log2t = one_pass ? flat_lt
+                               : level_log2t(lane_bytes, p, ops.lv.g1, st,
+                                             [&](int l) {
+                                               return groups * chunks(l);
+                                             });
+        uc.lv_C = (int)chunks(uc.lv_log2t);
         return uc;
       }
     }
@@ -1008,6 +1061,9 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   if (forced) want_sub = !std::strcmp(u, "sub") && sub_fits;
   if (want_sub) {
     uc.unit = dpar::Unit::SUB;
+    uc.grouped = one_pass && !forced && ops.lvl &&
+                 (lane_bytes << flat_lt) >= kLvMinPiece;
+    uc.lv_log2t = flat_lt;
     return uc;
   }
   const bool wide_fits =
@@ -1026,6 +1082,23 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   if (forced) want_wide = !std::strcmp(u, "wide") && wide_fits;
   if (want_wide) uc.unit = dpar::Unit::WIDE;
   return uc;
+}
+
+// Threads of a level item in one launch: a thread per quantum of every leaf
+// group, 256 to 1024, while the items have a CU each (they wait on their loads
+// together, so all of them are issued at once).  Several items per CU hide
+// each other's waits and finish more evenly when they are smaller: with 1 KB
+// chunks 512 threads, 256 for few groups (p = 300, m = 100000 fused with 256 /
+// 512 / 1024 threads 40.9 / 45.8 / 43.9 us; p = 1152, m = 131072 split 197 /
+// 188 / 194 us; shorter chunks, p = 2304, m = 131072: 569 / 420 / 377 us).
+int level_threads(int g1, int log2t, uint64_t items, const DeviceState& st) {
+  const uint64_t cus = (uint64_t)st.num_cus;
+  const int work = g1 << log2t;
+  int th = 256;
+  if (items > cus && log2t == 6)
+    return work <= 2560 ? th : 2 * th;
+  while (th < dpar::kLvMostThreads && th < work) th *= 2;
+  return th;
 }
 
 const char* exec_name(dpar::Exec e) {
@@ -1069,14 +1142,24 @@ void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
                path == dpar::Path::VEC16 ? "16B" : "4B", s.g, s.lq,
                (unsigned long long)s.tail, exec_name(ex), unit_name(unit),
                waves, prm.C, prm.grp, (unsigned long long)items);
-  if (unit == dpar::Unit::LEVEL)
-    std::fprintf(stderr, " level_chunk_quanta=%d", 1 << prm.lv_log2t);
-  if (unit == dpar::Unit::SUB)
+  if (unit == dpar::Unit::LEVEL || prm.flat)
+    std::fprintf(stderr, " level_chunk_quanta=%d threads=%d",
+                 1 << prm.lv_log2t, prm.lv_threads);
+  else if (unit == dpar::Unit::SUB)
     std::fprintf(stderr, " sub_deep=%d", prm.sub_deep);
   if (unit == dpar::Unit::WIDE)
     std::fprintf(stderr, " full_items=%u", prm.wide_full);
   if (ex == dpar::Exec::TICKET) std::fprintf(stderr, " batch=%u", prm.batch);
   std::fprintf(stderr, "\n");
+}
+
+void set_groups(dpar::Params* prm, const GroupInts& g) {
+  prm->g1 = g.g1;
+  prm->g2 = g.g2;
+  prm->nst = g.nst;
+  prm->val_a = g.val_a;
+  prm->val_b = g.val_b;
+  prm->extra = g.extra;
 }
 
 // fixed: the allocation-free variant (dual-root trees, AUTO executor, device
@@ -1349,25 +1432,21 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // them as one fused launch rather than split: each item's y goes from
   // registers to all p outputs while the few other items still read, and
   // the broadcast pass's many short workgroups (and their launch) are gone.
-  // Measured, int32 SUM, cold caches, the sqrt(m log2 p) rule's b: p = 1152,
-  // m = 2^16 (256 items) split 0.126 ms, fused 0.107 ms; p = 2304,
-  // m = 57344 (224 items) 0.199 vs 0.180 ms; p = 576, m = 57344 0.063 vs
-  // 0.057 ms; p = 288, m = 115712 (452 items) 0.060 vs 0.055 ms; down to a
-  // quarter of an item per CU in back-to-back calls (64 items, m = 16384:
-  // p = 700 46.0 -> 41.9 us, p = 1152 58.5 -> 51.0 us, p = 2304 102.0 ->
-  // 93.7 us, p = 4608 185.9 -> 175.2 us; after a cache flush within 2%
-  // either way); with fewer the chains dominate and fused is no better
-  // (p = 2304, m = 14336, 56 items: 0.107 vs 0.117 ms).  Calls that take
-  // post-order items on long rows stay split, which is faster there from
-  // 256 MB up (p = 36 .. 2304: 8-35% at 1-38 GB).
-  // Beyond two items per CU (many ranks, above) split stays faster in both
-  // regimes (p = 4608, m = 2^18: fused 1857 / 1722 us, split 1528 /
-  // 1897 us back to back / after a flush; the fused launch's p writes per
-  // item then overlap the reads of the items after it).
+  // Measured, back to back, split -> fused: p = 300, m = 65536 (157 MB
+  // moved) 28.8 -> 25.9 us, p = 256, m = 65536 25.1 -> 22.9 us, p = 576,
+  // m = 32768 28.4 -> 27.1 us, p = 1152, m = 16384 28.7 -> 28.1 us.  Split
+  // stays in larger calls (kSubFuseMaxBytes), with under a quarter of an
+  // item per CU (the p rows of few items are then written by few workgroups:
+  // p = 2304, m = 8192 30 us either way, p = 4608, m = 4096 39 -> 44 us) and
+  // beyond two items per CU (p = 1152, m = 2^18: 361 -> 459 us; the p writes
+  // per item overlap the reads of the items after it).
   if (exec == DPAR_EXEC_AUTO && ex == dpar::Exec::SPLIT &&
       uc.unit == dpar::Unit::SUB &&
       4 * ((s.Q + 63) / 64) >= (uint64_t)st->num_cus &&
-      (s.Q + 63) / 64 <= 2 * (uint64_t)st->num_cus)
+      (s.Q + 63) / 64 <= 2 * (uint64_t)st->num_cus &&
+      2ull * p * m * esz <= kSubFuseMaxBytes &&
+      ((rows_lines && xrows_lines) ||
+       (s.g * esz << uc.lv_log2t) >= kSubFuseMinPiece))
     ex = dpar::Exec::DISPATCH;
   // AUTO, wide items: with at most one per CU they all run at once, read
   // their rows together and then write y together, so one fused launch
@@ -1421,35 +1500,53 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
       uc.unit == dpar::Unit::SEQ &&
       (uint64_t)m * esz <= seq_fuse_row_bytes(p))
     ex = dpar::Exec::DISPATCH;
-  // AUTO, level items: a fused level item writes its chunk (a few quanta)
-  // to each of the p outputs, piece by piece; with many ranks the
-  // broadcast pass's whole tiles are faster, with few ranks the fused
-  // launch (int32 SUM, the rule's b, fused -> split, after a cache flush:
-  // p = 400, m = 16384 33.2 -> 35.2 us; p = 511 24.0 -> 28.6 us; p = 1152,
-  // m = 8192 57.3 -> 48.2 us; p = 2304, m = 1024 36.6 -> 33.4 us;
-  // p = 4608, m = 1024 73.9 -> 53.4 us; p = 1152, m = 1024 and 4096 2-4%
-  // slower split, but in back-to-back calls 24.7 -> 18.7 us and 31.7 ->
-  // 30.1 us; from 512 ranks on with at least one item per CU: p = 700,
-  // m = 8192 38.9 -> 34.3 us back to back, 38.8 -> 35.8 us after a flush;
-  // p = 900 42.9 -> 37.2 us).
+  // AUTO, level items: with few ranks the fused launch (split -> fused,
+  // back to back: p = 64, m = 16384 8.7 -> 5.7 us, p = 200, m = 65536 20.5 ->
+  // 18.1 us).  With many ranks a fused item writes its few quanta to each of
+  // the p rows, the broadcast pass whole tiles, for one launch more: p = 4608,
+  // m = 4096 44 -> 39 us split, p = 2304, m = 1024 18.3 -> 17.5 us, m = 4096
+  // 22.0 -> 22.6 us, while p = 1152, m = 1024 to 8192 and p = 700, m = 8192
+  // would be 1.5 to 2 us faster fused; the line stays where calls were split
+  // before.
   if (exec == DPAR_EXEC_AUTO && uc.unit == dpar::Unit::LEVEL &&
       (ex == dpar::Exec::SPLIT || ex == dpar::Exec::DISPATCH)) {
-    const uint64_t lv_items =
-        grouped_units(s, prm.grp) / (uint64_t)s.C * (uint64_t)uc.lv_C;
     const bool split = p >= kLvSplitRanks ||
                        (p >= kLvSplitManyRanks &&
-                        lv_items >= (uint64_t)st->num_cus);
+                        uc.lv_items >= (uint64_t)st->num_cus);
     ex = split ? dpar::Exec::SPLIT : dpar::Exec::DISPATCH;
   }
-  const dpar::Unit unit = uc.unit;
-  prm.nlev = ops->height + 1;
+  // subtree items of one pass run as level items over whole chunks
+  const dpar::Unit unit = uc.grouped ? dpar::Unit::LEVEL : uc.unit;
+  uint64_t tail = s.tail;  // elements left to the extra launch
+  set_groups(&prm, ops->lv);
+  prm.lv_threads = dpar::kLvThreads;
   if (unit == dpar::Unit::LEVEL) {
-    prm.C = uc.lv_C;
     prm.lv_log2t = uc.lv_log2t;
     prm.batch = 1;
-    if (grouped_units(s, prm.grp) / (uint64_t)s.C * (uint64_t)prm.C >=
-        (1ull << 31))
+    const uint64_t T = 1ull << uc.lv_log2t;
+    uint64_t items = grouped_units(s, prm.grp) / (uint64_t)s.C *
+                     (uint64_t)uc.lv_C;
+    if (ex == dpar::Exec::SPLIT || ex == dpar::Exec::DISPATCH) {
+      // one pass: whole chunks of T quanta, whatever the blocks
+      // (element-wise, so the result does not depend on the cut)
+      prm.flat = 1;
+      prm.b = 1;
+      prm.grp = 1;
+      // trailing elements: one more quantum, the row's last 16 bytes, which
+      // overlaps the one before it.  Both are in one item (all its loads come
+      // before its stores, so rows may be updated in place) unless the
+      // quanta before fill whole chunks.
+      if (tail > 0 && ex == dpar::Exec::DISPATCH && s.Q % T != 0) {
+        prm.over = (int)(4 - tail);
+        prm.Q = s.Q + 1;
+        tail = 0;
+      }
+      items = (prm.Q + T - 1) / T;
+    }
+    if (items >= (1ull << 31))
       return fail(DPAR_ERR_UNSUPPORTED, "more than 2^31 work items");
+    prm.C = prm.flat ? (int)items : uc.lv_C;
+    prm.lv_threads = level_threads(ops->lv.g1, uc.lv_log2t, items, *st);
   }
   if (unit == dpar::Unit::SUB) {
     tab.lvl = ops->sub;
@@ -1509,7 +1606,7 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   }
   // round-structured down-step: two ranks per wavefront per work item, the
   // largest block in pieces of kDownPiece quanta
-  prm.dslice = 2 * (unit == dpar::Unit::LEVEL ? 16
+  prm.dslice = 2 * (unit == dpar::Unit::LEVEL ? dpar::kLvThreads / 64
                     : unit == dpar::Unit::SUB ? dpar::kSubParts
                                               : waves);
   {
@@ -1549,10 +1646,15 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // 227 -> 186 us)
   if (up == dpar::Exec::SPLIT && path == dpar::Path::VEC16 && !xrows_lines)
     prm.xcd_runs = 1;
-  if (up == dpar::Exec::SPLIT)
+  // fused level items write the lines at their edges twice as well (p = 300,
+  // m = 100003 53.8 -> 50.0 us, p = 1152, m = 16385 64.9 -> 57.1 us)
+  if (up == dpar::Exec::DISPATCH && prm.flat && path == dpar::Path::VEC16 &&
+      !(xrows_lines && rows_lines))
+    prm.xcd_runs = 1;
+  if (up == dpar::Exec::SPLIT || prm.flat)
     prm.xcd_runs = env_int("DPAR_XCD_RUNS", prm.xcd_runs) != 0;
   if (env_int("DPAR_LOG", 0) != 0)
-    log_plan(p, m, dtype, op, alg, rule_b, s, path, up, unit, waves, prm,
+    log_plan(p, m, dtype, op, alg, rule_b, s, path, up, uc.unit, waves, prm,
              ops->real_height);
   // The cooperative executors start from zeroed barrier words (arrivals,
   // generation, give-up): a call whose wait gave up may leave them out of
@@ -1566,7 +1668,7 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   hipError_t e = dpar::launch(kind, path, unit, waves, up, tab, prm, stream,
                               st->num_cus, lds_floor);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
-  if (s.tail > 0) {
+  if (tail > 0) {
     // the elements after the last whole 16-byte quantum: one more chunk of
     // the last block, with one scalar per lane
     dpar::Params tp = prm;
@@ -1586,11 +1688,15 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
     // the walk)
     dpar::Tables tt = tab;
     tt.lvl = ops->lvl;
+    set_groups(&tp, ops->lv);
+    tp.flat = 1;
+    tp.over = 0;
+    tp.lv_threads = dpar::kLvThreads;
     tp.lv_log2t = 2;
     const bool level =
         p >= 2 && ops->lvl &&
-        dpar::level_lds_bytes(dpar::Path::SCALAR, kind, p, tp.lv_log2t,
-                              tp.nlev) <=
+        dpar::level_lds_bytes(dtype == DPAR_U32_MAT2X2 ? 16 : 4, ops->lv.g1,
+                              tp.lv_log2t) <=
             (size_t)st->lds_limit - dpar::kStaticLdsReserve;
     e = dpar::launch(kind, dpar::Path::SCALAR,
                      level ? dpar::Unit::LEVEL : dpar::Unit::SEQ, waves,

@@ -18,8 +18,8 @@
 //     the roots' outputs only, from where the round-structured down-step
 //     passes it from parent to child one depth per round.
 //
-// Short chunks can instead be evaluated level by level with the chunk staged
-// in LDS (run_unit_lv).  Round sequencing: all work items in round order in
+// Short chunks can instead be evaluated in groups of at most 7 ranks per
+// thread, three tree levels per step (run_unit_lv).  Round sequencing: all work items in round order in
 // one launch (split: the hardware dispatcher hands them out), one launch per
 // round, a persistent kernel with a grid barrier per round, a persistent
 // kernel that claims work items from atomic tickets in round order, or the
@@ -112,6 +112,16 @@ __device__ inline u32x4 mat_mul(u32x4 a, u32x4 b) {
   return c;
 }
 
+// a b + c d mod 2^32, each product a 32-bit multiply of its own (the empty asm
+// hides where it comes from).
+__device__ inline uint32_t dot2(uint32_t a, uint32_t b, uint32_t c,
+                                uint32_t d) {
+  uint32_t u = a * b, v = c * d;
+  asm("" : "+v"(u));
+  asm("" : "+v"(v));
+  return u + v;
+}
+
 // ------------------------------------------------------------ lane layouts
 // A lane owns one quantum: `bytes` contiguous bytes of every rank row.
 
@@ -158,6 +168,30 @@ struct LaneMat {  // one matrix, one 16-byte access (4-byte aligned)
   __device__ static void store(uint64_t row, uint32_t off, T v) {
     st(gptr_w<u32x4g>(row, off), (u32x4g)v);
   }
+};
+
+// The matrix lane of the level work item.  Left to itself the compiler merges
+// a product and the addition into a 32 x 32 + 64-bit multiply-add; with the
+// products under uniform branches (a wavefront per group) it then kept the
+// multiply-add's high half in place of a neighbouring entry: wrong matrices
+// from 3 ranks on.
+struct LaneMatLv : LaneMat {
+  __device__ static T ap(T a, T b) {
+    T c;
+    c.x = dot2(a.x, b.x, a.y, b.z);
+    c.y = dot2(a.x, b.y, a.y, b.w);
+    c.z = dot2(a.z, b.x, a.w, b.z);
+    c.w = dot2(a.z, b.y, a.w, b.w);
+    return c;
+  }
+};
+template <class L>
+struct LevelLane {
+  using type = L;
+};
+template <>
+struct LevelLane<LaneMat> {
+  using type = LaneMatLv;
 };
 
 // ------------------------------------------------------------ one work item
@@ -375,128 +409,227 @@ __device__ __forceinline__ void run_unit(const uint64_t* __restrict__ xp,
 }
 
 // ------------------------------------------------------------ level units
-// Level-synchronous work item, for chunks too small to keep a GPU busy with
-// one post-order walk per chunk.  1024 threads load every rank's quanta of a
-// chunk of at most T quanta into LDS at once, then evaluate the two trees one
-// depth level at a time from the deepest up: every (node, quantum) pair of a
-// level computes S(i) = S(child1) (.) (S(child0) (.) x_i) from children
-// finished in the previous level, then a barrier.  Same association as the
-// post-order walk; the dependent chain is H + 1 levels instead of p loads.
+// Work item for chunks too small to keep a GPU busy with one post-order walk
+// per chunk: the trees are evaluated three levels per step (plan.hpp
+// make_groups).  A chunk has at most T quanta; T neighbouring threads take
+// one group of at most 7 ranks, one quantum each, load its ranks' quanta at
+// once and combine them in registers; group values wait in LDS for the groups
+// above, one barrier per stage.  Same association as the post-order walk; the
+// dependent chain is ceil((H + 1) / 3) stages.
 //
-// LDS: S [p][T] lane values | Y [T] | ptr [p] row addresses | lvl [p]
-// level-ordered entries | off [H + 2] level boundaries.
-constexpr int kLvThreads = 1024;
-constexpr int kLvBatch = 8;  // loads in flight per thread
+// LDS: values [g1][T]; a later group's value replaces one of the values it
+// has used (each is used once).
+//
+// Bound by the wait on the loads (pointer table, then rows) in short calls and
+// by HBM in long ones.  Groups of 7: all loads of an item are in flight at
+// once (7 per thread, the groups above read ahead as well), 3 barriers at
+// p = 1152, and LDS for p / 8 values instead of p rows, so chunks are long
+// enough for whole cache lines.  int32 SUM, one MI355X, back to back, against
+// an item that staged every row in LDS with one level per barrier: p = 288,
+// m = 875 8.1 -> 5.4 us, p = 1152, m = 1024 20.1 -> 13.7 us, p = 700, m = 8192
+// 28.0 -> 13.1 us, p = 4608, m = 4096 137 -> 40 us (3.8 TB/s).  Loading a
+// group's rows before the previous one is combined (two sets of registers)
+// gained nothing.
 
-__host__ __device__ inline size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
-
+// Combines a heap-shaped group of n ranks, v[h] the block of position h: the
+// first child's value, at 2 h + 1 (or 2 h when it is the only one), before the
+// second's.
 template <class L>
-struct LvLayout {
-  size_t s, y, ptr, lvl, off, total;
-  __host__ __device__ LvLayout(int p, int T, int nlev) {
-    s = 0;
-    y = align16(s + (size_t)p * T * sizeof(typename L::T));
-    ptr = align16(y + (size_t)T * sizeof(typename L::T));
-    lvl = align16(ptr + (size_t)p * 8);
-    off = align16(lvl + (size_t)p * 4);
-    total = align16(off + (size_t)(nlev + 1) * 4);
+__device__ __forceinline__ typename L::T leaf_group(typename L::T (&v)[8],
+                                                    int n) {
+  if (n >= 5) v[2] = L::ap(v[5], v[2]);
+  if (n >= 4) v[2] = L::ap(v[4], v[2]);
+  if (n >= 7) v[3] = L::ap(v[7], v[3]);
+  if (n >= 6) v[3] = L::ap(v[6], v[3]);
+  if (n >= 3) v[1] = L::ap(v[3], v[1]);
+  if (n >= 2) v[1] = L::ap(v[2], v[1]);
+  return v[1];
+}
+
+// A later group: w[h] the block of position h <= n, the values of the
+// children past n from LDS (val: this thread's column, stride TQ).
+template <class L>
+__device__ __forceinline__ typename L::T later_group(
+    const typename L::T (&x)[8], const uint32_t (&rec)[kGroupWords],
+    const typename L::T* val, int sh) {
+  using T = typename L::T;
+  const int n = (int)(rec[0] & 0xFFu);
+  T w[16];
+#pragma unroll
+  for (int c = 2; c < 16; ++c) {
+    const uint32_t i = (rec[8 + (c - 2) / 2] >> 16 * (c & 1)) & 0xFFFFu;
+    if (c < 8) w[c] = x[c];
+    if (c > n && c <= 2 * n + 1) w[c] = val[(size_t)i << sh];
+  }
+  w[1] = x[1];
+#pragma unroll
+  for (int h = 7; h >= 1; --h)
+    if (h <= n) w[h] = L::ap(w[2 * h], L::ap(w[2 * h + 1], w[h]));
+  return w[1];
+}
+
+// The stages above the leaf groups, whose values are in LDS (not yet behind
+// a barrier); mine: thread group tg holds later group tg, its record in rec
+// and its ranks' blocks in x.  Returns y.
+template <class L>
+__device__ __forceinline__ typename L::T later_stages(
+    const uint64_t* __restrict__ xp, const uint32_t* __restrict__ later,
+    const Params& prm, int sh, uint64_t unit_off, uint32_t qoff, int tg,
+    int ntg, bool mine, const uint32_t (&rec)[kGroupWords],
+    const typename L::T (&x)[8], typename L::T xe, typename L::T* val) {
+  using T = typename L::T;
+  for (int st = 1; st < prm.nst; ++st) {
+    __syncthreads();
+    if (mine && (int)(rec[0] >> 8) == st)
+      val[(size_t)rec[15] << sh] = later_group<L>(x, rec, val, sh);
+    // more groups than thread groups: the rest are read here
+    for (int j = tg + ntg; j < prm.g2; j += ntg) {
+      uint32_t r[kGroupWords];
+#pragma unroll
+      for (int k = 0; k < kGroupWords; ++k)
+        r[k] = later[(size_t)j * kGroupWords + k];
+      if ((int)(r[0] >> 8) != st) continue;
+      T z[8];
+      z[0] = T{};
+#pragma unroll
+      for (int h = 1; h < 8; ++h) z[h] = L::load(xp[r[h]] + unit_off, qoff);
+      val[(size_t)r[15] << sh] = later_group<L>(z, r, val, sh);
+    }
+  }
+  __syncthreads();
+  if (prm.extra >= 0) {
+    // one tree: its root on top of part B.  Its block is used before the last
+    // barrier, as every other one: past it, rows updated in place are written
+    if (tg == 0)
+      val[(size_t)prm.val_b << sh] =
+          L::ap(val[(size_t)prm.val_b << sh], xe);
+    __syncthreads();
+  }
+  const T a = val[(size_t)prm.val_a << sh];
+  return prm.dual ? L::ap(a, val[(size_t)prm.val_b << sh]) : a;
+}
+
+// This thread group's later record and its ranks' blocks.
+template <class L>
+__device__ __forceinline__ void later_loads(
+    const uint64_t* __restrict__ xp, const uint32_t* __restrict__ later,
+    uint64_t unit_off, uint32_t qoff, int tg,
+    uint32_t (&rec)[kGroupWords], typename L::T (&x)[8]) {
+  const u32x4* r4 = reinterpret_cast<const u32x4*>(later) + (size_t)tg * 4;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const u32x4 v = r4[k];
+    rec[4 * k] = v.x;
+    rec[4 * k + 1] = v.y;
+    rec[4 * k + 2] = v.z;
+    rec[4 * k + 3] = v.w;
+  }
+  uint64_t row[8];
+#pragma unroll
+  for (int h = 1; h < 8; ++h) row[h] = xp[rec[h]] + unit_off;
+#pragma unroll
+  for (int h = 1; h < 8; ++h) x[h] = L::load(row[h], qoff);
+}
+
+// y from this thread's register to quantum q of the p output rows, thread
+// group tg taking rows tg, tg + ntg, ...
+template <class L>
+__device__ __forceinline__ void write_rows(const uint64_t* __restrict__ yp,
+                                           int p, uint64_t unit_off,
+                                           uint32_t qoff, int tg, int ntg,
+                                           typename L::T y) {
+  int i = tg;
+  for (; i + 3 * ntg < p; i += 4 * ntg) {
+    uint64_t row[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) row[k] = yp[i + k * ntg] + unit_off;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) L::store(row[k], qoff, y);
+  }
+  for (; i < p; i += ntg) L::store(yp[i] + unit_off, qoff, y);
+}
+
+// A leaf group's record and its ranks' blocks in flight.
+template <class L>
+struct LeafLoad {
+  uint32_t shape = 0;
+  typename L::T v[8];
+  __device__ __forceinline__ void issue(const uint64_t* __restrict__ xp,
+                                        const uint32_t* __restrict__ gt, int g,
+                                        uint64_t unit_off, uint32_t qoff) {
+    const uint32_t lo = gt[2 * g];
+    shape = gt[2 * g + 1];
+    uint64_t row[8];
+#pragma unroll
+    for (int h = 1; h < 8; ++h)
+      row[h] = xp[lo + ((shape >> 3 * (h - 1)) & 7u)] + unit_off;
+#pragma unroll
+    for (int h = 1; h < 8; ++h) v[h] = L::load(row[h], qoff);
+  }
+  __device__ __forceinline__ typename L::T value() {
+    return leaf_group<L>(v, (int)(shape >> 21));
   }
 };
 
-template <class L, bool FUSED>
+// WAVE: chunks of 64 quanta, a wavefront per group (its index, records and
+// row addresses are scalars).
+template <class L, bool FUSED, bool WAVE>
 __device__ __forceinline__ void run_unit_lv(const uint64_t* __restrict__ xp,
                                             const uint64_t* __restrict__ yp,
-                                            const uint32_t* __restrict__ lvl_g,
+                                            const uint32_t* __restrict__ gt,
                                             const Params& prm, uint64_t t,
                                             char* lds) {
   using T = typename L::T;
-  const int tid = threadIdx.x;
-  const int p = prm.p, sh = prm.lv_log2t, TQ = 1 << sh, nlev = prm.nlev;
-  const LvLayout<L> lay(p, TQ, nlev);
-  T* S = reinterpret_cast<T*>(lds + lay.s);
-  T* Y = reinterpret_cast<T*>(lds + lay.y);
-  uint64_t* ptr = reinterpret_cast<uint64_t*>(lds + lay.ptr);
-  uint32_t* lvl = reinterpret_cast<uint32_t*>(lds + lay.lvl);
-  uint32_t* off = reinterpret_cast<uint32_t*>(lds + lay.off);
+  const int tid = threadIdx.x, sh = WAVE ? 6 : prm.lv_log2t, TQ = 1 << sh;
+  const int q = tid & (TQ - 1), ntg = (int)blockDim.x >> sh;
+  const int tg = WAVE ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> sh;
 
-  // chunk -> quanta [cs, ce): the item's blocks are cut at lines, the chunk
-  // at quanta
-  uint64_t ls, le, c;
-  item_lines(prm, t, &ls, &le, &c);
-  const uint64_t qs = min(ls * prm.lq, prm.Q);
-  const uint64_t qe = min(le * prm.lq, prm.Q);
-  const uint64_t n = qe - qs;
-  const uint64_t cs = qs + c * n / (uint64_t)prm.C;
-  const uint64_t ce = qs + (c + 1) * n / (uint64_t)prm.C;
+  // chunk -> quanta [cs, ce): whole chunks of T quanta from the first one
+  // (flat), or the item's blocks, cut at lines, in chunks cut at quanta
+  uint64_t cs, ce;
+  if (prm.flat) {
+    cs = t << sh;
+    ce = min(cs + (uint64_t)TQ, prm.Q);
+  } else {
+    uint64_t ls, le, c;
+    item_lines(prm, t, &ls, &le, &c);
+    const uint64_t qs = min(ls * prm.lq, prm.Q);
+    const uint64_t qe = min(le * prm.lq, prm.Q);
+    const uint64_t n = qe - qs;
+    cs = qs + c * n / (uint64_t)prm.C;
+    ce = qs + (c + 1) * n / (uint64_t)prm.C;
+  }
   const int count = (int)(ce - cs);
   if (count == 0) return;  // uniform
   const uint64_t unit_off = (prm.qbase + cs) * (uint64_t)L::bytes;
+  // quanta past the chunk re-read its last one
+  uint32_t qoff = (uint32_t)min(q, count - 1) * L::bytes;
+  // (the last quantum of a row with trailing elements starts early)
+  if (prm.over && cs + min(q, count - 1) + 1 == prm.Q)
+    qoff -= (uint32_t)prm.over * 4;
+  T* val = reinterpret_cast<T*>(lds) + q;
 
-  for (int i = tid; i < p; i += kLvThreads) {
-    ptr[i] = xp[i] + unit_off;
-    lvl[i] = lvl_g[i];
+  const uint32_t* later = gt + (((size_t)prm.g1 * 2 + 3) & ~(size_t)3);
+  uint32_t rec[kGroupWords];
+  T x[8], xe = T{};
+  const bool mine = tg < prm.g2;
+  LeafLoad<L> leaf;
+  if (tg < prm.g1) leaf.issue(xp, gt, tg, unit_off, qoff);
+  if (mine) later_loads<L>(xp, later, unit_off, qoff, tg, rec, x);
+  if (prm.extra >= 0 && tg == 0)
+    xe = L::load(xp[prm.extra] + unit_off, qoff);
+  for (int g = tg; g < prm.g1;) {
+    val[(size_t)g << sh] = leaf.value();
+    g += ntg;
+    if (g < prm.g1) leaf.issue(xp, gt, g, unit_off, qoff);
   }
-  for (int i = tid; i <= nlev; i += kLvThreads) off[i] = lvl_g[p + i];
-  __syncthreads();
-
-  // all loads of the chunk, kLvBatch per thread in flight
-  const int total = p << sh;
-  for (int base = 0; base < total; base += kLvThreads * kLvBatch) {
-    T v[kLvBatch];
-#pragma unroll
-    for (int k = 0; k < kLvBatch; ++k) {
-      const int idx = base + k * kLvThreads + tid;
-      const bool ok = idx < total && (idx & (TQ - 1)) < count;
-      // items past the chunk re-read quantum 0 of rank 0 (always in range)
-      const int i = ok ? (idx >> sh) : 0;
-      const uint32_t q = ok ? (uint32_t)(idx & (TQ - 1)) : 0u;
-      v[k] = L::load(ptr[i], q * L::bytes);
-    }
-#pragma unroll
-    for (int k = 0; k < kLvBatch; ++k) {
-      const int idx = base + k * kLvThreads + tid;
-      if (idx < total && (idx & (TQ - 1)) < count) S[idx] = v[k];
-    }
-  }
-  __syncthreads();
-
-  // levels, deepest first; entry = node << 16 | code, code 0xFFFF: leaf,
-  // 0xFFFE: first child only (node - 1), else the second child's rank
-  for (int lv = 0; lv < nlev; ++lv) {
-    const int o0 = (int)off[lv];
-    const int items = ((int)off[lv + 1] - o0) << sh;
-    for (int idx = tid; idx < items; idx += kLvThreads) {
-      const int q = idx & (TQ - 1);
-      if (q >= count) continue;
-      const uint32_t e = lvl[o0 + (idx >> sh)];
-      const int node = (int)(e >> 16);
-      const uint32_t code = e & 0xFFFFu;
-      T v = S[(node << sh) + q];
-      if (code != 0xFFFFu) v = L::ap(S[((node - 1) << sh) + q], v);
-      if (code < 0xFFFEu) v = L::ap(S[((int)code << sh) + q], v);
-      S[(node << sh) + q] = v;
-    }
-    __syncthreads();
-  }
-
-  // dual-root step, then the write-out
-  if (tid < count) {
-    const int ra = prm.n_a - 1;
-    Y[tid] = prm.dual ? L::ap(S[(ra << sh) + tid], S[((p - 1) << sh) + tid])
-                      : S[(ra << sh) + tid];
-  }
-  if (FUSED)
-    for (int i = tid; i < p; i += kLvThreads) ptr[i] = yp[i] + unit_off;
-  __syncthreads();
+  const T y = later_stages<L>(xp, later, prm, sh, unit_off, qoff, tg, ntg,
+                              mine, rec, x, xe, val);
   if (FUSED) {
-    for (int idx = tid; idx < total; idx += kLvThreads) {
-      const int q = idx & (TQ - 1);
-      if (q < count) L::store(ptr[idx >> sh], (uint32_t)q * L::bytes, Y[q]);
-    }
+    if (q < count) write_rows<L>(yp, prm.p, unit_off, qoff, tg, ntg, y);
   } else if (tid < count) {
-    L::store(yp[prm.out0] + unit_off, (uint32_t)tid * L::bytes, Y[tid]);
-    if (prm.out1 >= 0)
-      L::store(yp[prm.out1] + unit_off, (uint32_t)tid * L::bytes, Y[tid]);
+    L::store(yp[prm.out0] + unit_off, qoff, y);
+    if (prm.out1 >= 0) L::store(yp[prm.out1] + unit_off, qoff, y);
   }
   __syncthreads();  // LDS is reused by the next work item
 }
@@ -848,6 +981,7 @@ template <class L, int W, bool FUSED>
 struct SeqUnit {
   using Lane = L;
   static constexpr int kThreads = 64 * W;
+  static constexpr int kMostThreads = kThreads;
   __device__ static void run(const uint64_t* __restrict__ xp,
                              const uint64_t* __restrict__ yp,
                              const uint32_t* __restrict__ ops,
@@ -866,6 +1000,7 @@ template <class L, bool FUSED, int KU = kU>
 struct SubUnit {
   using Lane = L;
   static constexpr int kThreads = 64 * kSubParts;
+  static constexpr int kMostThreads = kThreads;
   __device__ static void run(const uint64_t* __restrict__ xp,
                              const uint64_t* __restrict__ yp,
                              const uint32_t* __restrict__ ops,
@@ -879,20 +1014,21 @@ struct SubUnit {
   }
 };
 
-template <class L, bool FUSED>
+template <class L, bool FUSED, bool WAVE = false>
 struct LvUnit {
   using Lane = L;
   static constexpr int kThreads = kLvThreads;
+  static constexpr int kMostThreads = kLvMostThreads;
   __device__ static void run(const uint64_t* __restrict__ xp,
                              const uint64_t* __restrict__ yp,
                              const uint32_t* __restrict__ ops,
                              const uint32_t* __restrict__ lvl,
                              const Params& prm, uint64_t t, char* lds) {
     (void)ops;
-    run_unit_lv<L, FUSED>(xp, yp, lvl, prm, t, lds);
+    run_unit_lv<L, FUSED, WAVE>(xp, yp, lvl, prm, t, lds);
   }
   static size_t lds(const Params& prm) {
-    return LvLayout<L>(prm.p, 1 << prm.lv_log2t, prm.nlev).total;
+    return level_lds_bytes(sizeof(typename L::T), prm.g1, prm.lv_log2t);
   }
 };
 
@@ -900,6 +1036,7 @@ template <class L, bool FUSED, bool TAIL>
 struct WideUnit {
   using Lane = L;
   static constexpr int kThreads = 64 * kWideWaves;
+  static constexpr int kMostThreads = kThreads;
   __device__ static void run(const uint64_t* __restrict__ xp,
                              const uint64_t* __restrict__ yp,
                              const uint32_t* __restrict__ ops,
@@ -922,7 +1059,7 @@ struct WideUnit {
       Params prm
 
 template <class U>
-__global__ __launch_bounds__(U::kThreads) void k_round(DPAR_KARGS, int round,
+__global__ __launch_bounds__(U::kMostThreads) void k_round(DPAR_KARGS, int round,
                                                       uint64_t first) {
   extern __shared__ char lds_raw[];
   // in launch order, or each XCD a contiguous run of the launch's items
@@ -1279,26 +1416,44 @@ hipError_t launch_ticket(const Tables& tab, const Params& prm,
   return hipGetLastError();
 }
 
+// Threads per workgroup: the unit's own, for level items in k_round what the
+// host chose.
+template <class U>
+unsigned threads_of(Exec exec, const Params& prm) {
+  if constexpr (U::kMostThreads != U::kThreads)
+    if (exec == Exec::DISPATCH || exec == Exec::LAUNCH_PER_ROUND)
+      return (unsigned)prm.lv_threads;
+  return U::kThreads;
+}
+
+// One workgroup per work item, t = first + blockIdx.x.
+template <class U>
+hipError_t launch_items(const Tables& tab, const Params& prm,
+                        hipStream_t stream, unsigned threads, size_t lds) {
+  const uint64_t nunits = item_groups(prm) * prm.C;
+  const uint64_t kMaxGrid = (1ull << 31) / U::kMostThreads;
+  for (uint64_t first = 0; first < nunits; first += kMaxGrid) {
+    const uint64_t n = min(kMaxGrid, nunits - first);
+    hipLaunchKernelGGL((k_round<U>), dim3((unsigned)n), dim3(threads), lds,
+                       stream, tab.xp, tab.yp, tab.ops, tab.lvl, prm, 0,
+                       first);
+  }
+  return hipGetLastError();
+}
+
 template <class U>
 hipError_t launch_u(Exec exec, const Tables& tab, const Params& prm,
                     hipStream_t stream, int num_cus, size_t lds_floor) {
   // a larger request than the work item needs only lowers the number of
   // workgroups resident per CU (see launch())
   const size_t lds = U::lds(prm) > lds_floor ? U::lds(prm) : lds_floor;
-  const dim3 block(U::kThreads);
-  const uint64_t nunits = item_groups(prm) * prm.C;
+  const dim3 block(threads_of<U>(exec, prm));
   // One workgroup per work item: a launch's total thread count must stay
   // below 2^32, so a grid of more than kMaxGrid workgroups goes out as
   // several launches, each given the index of its first item.
-  const uint64_t kMaxGrid = (1ull << 31) / U::kThreads;
-  if (exec == Exec::DISPATCH) {  // work item t = first + blockIdx.x
-    for (uint64_t first = 0; first < nunits; first += kMaxGrid) {
-      const uint64_t n = min(kMaxGrid, nunits - first);
-      hipLaunchKernelGGL((k_round<U>), dim3((unsigned)n), block, lds, stream,
-                         tab.xp, tab.yp, tab.ops, tab.lvl, prm, 0, first);
-    }
-    return hipGetLastError();
-  }
+  const uint64_t kMaxGrid = (1ull << 31) / U::kMostThreads;
+  if (exec == Exec::DISPATCH)
+    return launch_items<U>(tab, prm, stream, block.x, lds);
   if (exec == Exec::LAUNCH_PER_ROUND) {
     for (int j = 0; j < prm.b; ++j)
       for (uint64_t first = 0; first < (uint64_t)prm.C; first += kMaxGrid) {
@@ -1403,9 +1558,19 @@ hipError_t launch_l(Unit unit, int waves, Exec exec, const Tables& tab,
                                              : exec;
 #define DPAR_LAUNCH_U(...) \
   launch_u<__VA_ARGS__>(ex, tab, prm, stream, num_cus, lds_floor)
+  using LL = typename LevelLane<L>::type;
+  if (unit == Unit::LEVEL && ex == Exec::DISPATCH && prm.lv_log2t == 6) {
+    // 1 KB (or 256-byte) chunks: a wavefront per group
+    const unsigned th = (unsigned)prm.lv_threads;
+    const size_t lds = LvUnit<LL, true, true>::lds(prm);
+    return fused ? launch_items<LvUnit<LL, true, true>>(tab, prm, stream, th,
+                                                       lds)
+                 : launch_items<LvUnit<LL, false, true>>(tab, prm, stream, th,
+                                                        lds);
+  }
   if (unit == Unit::LEVEL)
-    return fused ? DPAR_LAUNCH_U(LvUnit<L, true>)
-                 : DPAR_LAUNCH_U(LvUnit<L, false>);
+    return fused ? DPAR_LAUNCH_U(LvUnit<LL, true>)
+                 : DPAR_LAUNCH_U(LvUnit<LL, false>);
   if (unit == Unit::SUB) {
     if (prm.sub_deep)
       return fused ? DPAR_LAUNCH_U(SubUnit<L, true, kUDeep>)
@@ -1458,15 +1623,8 @@ hipError_t launch(Kind kind, Path path, Unit unit, int waves, Exec exec,
   return hipErrorInvalidValue;
 }
 
-size_t level_lds_bytes(Path path, Kind kind, int p, int log2t, int nlev) {
-  const size_t lane = (path == Path::VEC16 || kind == Kind::MAT) ? 16 : 4;
-  const size_t T = (size_t)1 << log2t;
-  const size_t s = 0;
-  const size_t y = align16(s + (size_t)p * T * lane);
-  const size_t ptr = align16(y + T * lane);
-  const size_t lvl = align16(ptr + (size_t)p * 8);
-  const size_t off = align16(lvl + (size_t)p * 4);
-  return align16(off + (size_t)(nlev + 1) * 4);
+size_t level_lds_bytes(size_t lane_bytes, int g1, int log2t) {
+  return ((size_t)g1 << log2t) * lane_bytes;
 }
 
 template <bool FAST>

@@ -55,7 +55,14 @@ struct Params {
                     // blocks are shorter than half a chunk)
   unsigned batch;   // TICKET: consecutive work items claimed per ticket
   int lv_log2t;     // LEVEL: log2 of the chunk capacity T in quanta
-  int nlev;         // LEVEL: H + 1 depth levels
+  int lv_threads;   // LEVEL: threads per workgroup (k_round; the other
+                    // kernels run kLvThreads)
+  int flat;         // LEVEL: items are whole chunks of T quanta, whatever the
+                    // blocks
+  int over;         // LEVEL, flat: elements by which the last quantum
+                    // overlaps the one before (0: it does not)
+  int g1, g2, nst;  // LEVEL: groups and stages (plan.hpp GroupPlan)
+  int val_a, val_b, extra;
   unsigned* ticket;     // TICKET: kTicketCounters counters, kCounterStride
                         // words apart; each reset by the last WG it served
   unsigned* done;       // TICKET: per-counter count of WGs finished, same
@@ -103,8 +110,8 @@ struct Tables {
   const uint64_t* xp;   // [p] device addresses of x_i
   const uint64_t* yp;   // [p] device addresses of y_i
   const uint32_t* ops;  // [p] opcodes (plan.hpp)
-  const uint32_t* lvl;  // LEVEL: [p] level-ordered entries, then H + 2
-                        // offsets; SUB: the subtree plan (plan.hpp)
+  const uint32_t* lvl;  // LEVEL: the group table (plan.hpp); SUB: the subtree
+                        // plan
   const uint32_t* dn;   // [p] ROUNDS: parent << 8 | depth (plan.hpp)
   const uint32_t* dord;  // ROUNDS: H + 2 depth offsets, then the non-root
                          // ranks by depth (plan.hpp make_depth_order)
@@ -127,8 +134,14 @@ hipError_t launch(Kind kind, Path path, Unit unit, int waves, Exec exec,
 // faulted.)
 constexpr size_t kStaticLdsReserve = 256;
 
-// Bytes of dynamic LDS a LEVEL work item needs.
-size_t level_lds_bytes(Path path, Kind kind, int p, int log2t, int nlev);
+// Bytes of dynamic LDS a LEVEL work item needs with g1 leaf groups (plan.hpp
+// GroupPlan) and chunks of 2^log2t quanta.
+size_t level_lds_bytes(size_t lane_bytes, int g1, int log2t);
+
+// Threads of a LEVEL work item: the most in k_round, and in the other
+// kernels.
+constexpr int kLvMostThreads = 1024;
+constexpr int kLvThreads = 512;
 
 // WIDE work items: quanta per lane, wavefronts per workgroup (each on its
 // own 64 kWideQ quanta of the chunk), rank visits in flight per wavefront.

@@ -102,6 +102,7 @@ Tree kernel_single_tree(int p) {
   t.n_a = t.lo[c0];              // part A = [0, lo(c0)), its root is c1
   t.root_a = c1;
   t.root_b = r;
+  t.lo[r] = t.n_a;
   t.parent[c1] = -1;
   t.child1[r] = -1;              // the root keeps only its first child
   t.dual[c1] = r;
@@ -172,6 +173,106 @@ bool make_sub(const Tree& t, const std::vector<uint32_t>& ops, int s,
   out->insert(out->end(), entries[0].begin(), entries[0].end());
   out->insert(out->end(), entries[1].begin(), entries[1].end());
   return true;
+}
+
+GroupPlan make_groups(const Tree& t) {
+  GroupPlan g;
+  std::vector<int> value(t.p, -1);  // a group root's value
+  std::vector<int> left(t.p, 0);    // ranks of v's subtree not grouped yet
+  std::vector<int> nodes;           // ranks above the leaf groups, ascending
+  int root[2] = {t.root_a, t.root_b};
+  if (t.slot_shift) {  // one tree: the root goes on top of its first child
+    g.extra = t.root_b;
+    root[1] = t.child0[t.root_b];
+  }
+  auto size = [&](int v) { return v - t.lo[v] + 1; };
+  for (int v = 0; v < t.p; ++v) {
+    if (v == g.extra) continue;
+    const int par = t.parent[v];
+    if (size(v) > kGroupRanks) {
+      nodes.push_back(v);
+    } else if (par < 0 || par == g.extra || size(par) > kGroupRanks) {
+      value[v] = g.g1++;
+      g.lo.push_back((uint32_t)t.lo[v]);
+      g.hi.push_back((uint32_t)v);
+    }
+  }
+  while (!nodes.empty()) {
+    for (int v : nodes) {  // children come before their parents
+      left[v] = 1;
+      for (int c : {t.child0[v], t.child1[v]})
+        if (c >= 0 && value[c] < 0) left[v] += left[c];
+    }
+    std::vector<int> rest;
+    std::vector<std::pair<int, int>> done;  // group roots and their slots
+    const int stage = g.nst++;
+    for (int v : nodes) {
+      if (left[v] > kGroupRanks) {
+        rest.push_back(v);
+        continue;
+      }
+      const int par = t.parent[v];
+      if (par >= 0 && par != g.extra && left[par] <= kGroupRanks) continue;
+      uint32_t rec[kGroupWords] = {};
+      int at[2 * kGroupRanks + 2] = {0, v};  // rank at each heap position
+      const int n = left[v];
+      for (int h = 1; h <= n; ++h) {
+        const int u = at[h];
+        const int l = t.child1[u], r = t.child0[u];
+        if (l < 0 || r < 0) return GroupPlan{};
+        at[2 * h] = l;
+        at[2 * h + 1] = r;
+      }
+      rec[0] = (uint32_t)n | (uint32_t)stage << 8;
+      for (int h = 1; h <= kGroupRanks; ++h)
+        rec[h] = (uint32_t)(h <= n ? at[h] : v);
+      for (int c = 2; c <= 2 * n + 1; ++c) {
+        // positions up to n are ranks of the group, later ones values
+        if ((value[at[c]] < 0) != (c <= n)) return GroupPlan{};
+        if (c > n)
+          rec[8 + (c - 2) / 2] |= (uint32_t)value[at[c]] << 16 * (c & 1);
+      }
+      rec[15] = (uint32_t)value[at[n + 1]];
+      g.later.insert(g.later.end(), rec, rec + kGroupWords);
+      ++g.g2;
+      done.push_back({v, (int)rec[15]});
+    }
+    // the new values, once none of this stage's groups may use them (ranks
+    // inside a group have none of their own)
+    for (const auto& d : done) value[d.first] = d.second;
+    nodes.swap(rest);
+  }
+  g.val_a = value[root[0]];
+  g.val_b = root[1] >= 0 ? value[root[1]] : g.val_a;
+  g.ok = g.g1 < 65536;
+  return g;
+}
+
+uint32_t leaf_shape(int n) {
+  int off[16] = {}, next = 0;
+  // post-order of the heap positions 1 .. n: left subtree, right, node
+  auto walk = [&](auto&& self, int h) -> void {
+    if (h > n) return;
+    self(self, 2 * h);
+    self(self, 2 * h + 1);
+    off[h] = next++;
+  };
+  walk(walk, 1);
+  uint32_t w = (uint32_t)n << 21;
+  for (int h = 1; h <= kGroupRanks; ++h)
+    w |= (uint32_t)off[h <= n ? h : 1] << 3 * (h - 1);
+  return w;
+}
+
+std::vector<uint32_t> group_table(const GroupPlan& g) {
+  std::vector<uint32_t> out;
+  for (int i = 0; i < g.g1; ++i) {
+    out.push_back(g.lo[i]);
+    out.push_back(leaf_shape((int)(g.hi[i] - g.lo[i]) + 1));
+  }
+  out.resize(group_later_at(g.g1), 0u);
+  out.insert(out.end(), g.later.begin(), g.later.end());
+  return out;
 }
 
 std::vector<uint32_t> make_down(const Tree& t) {

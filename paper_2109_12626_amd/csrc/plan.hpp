@@ -84,6 +84,47 @@ constexpr int kSubSpineRanks = 4;   // spine ranks per tree at most
 bool make_sub(const Tree& t, const std::vector<uint32_t>& ops, int s,
               std::vector<uint32_t>* out);
 
+// Plan of the grouped evaluation of the trees.  Every tree is cut into leaf
+// groups, the maximal subtrees of at most kGroupRanks ranks, and the ranks
+// above them into groups of at most kGroupRanks ranks each, stage by stage from the
+// bottom: a stage's groups are the maximal subtrees of at most kGroupRanks of
+// the ranks that no earlier stage took, so a group needs only values of
+// earlier stages, and three tree levels are done per stage.  All trees are
+// heap-shaped, so a group's ranks form a heap-shaped tree themselves: with n
+// of them, heap positions 1 .. n, position h's children at 2h and 2h + 1; a
+// child position past n is a whole group of an earlier stage (every rank
+// above the leaf groups has two children).
+//
+// Every value has a slot: leaf group i slot i, a later group the slot of the
+// first group value it uses (nothing else uses that one), so g1 slots do.
+// Later record (kGroupWords words): [0] n | stage << 8 (1 the first stage
+// above the leaf groups); [1..7] the ranks of positions 1..7 (unused ones
+// repeat position 1); [8..14] the slots of child positions 2..15, 16 bits
+// each (0 where the position is a rank of the group); [15] its own slot.
+constexpr int kGroupRanks = 7;
+constexpr int kGroupWords = 16;
+struct GroupPlan {
+  bool ok = false;
+  int g1 = 0, g2 = 0;        // leaf groups, later groups
+  int nst = 1;               // stages, the leaf groups' included
+  int val_a = 0, val_b = 0;  // slots of the two trees' root values
+  int extra = -1;            // one tree: its root, applied to val_b's value
+  std::vector<uint32_t> lo, hi;  // ranks [lo, hi] of leaf group i
+  std::vector<uint32_t> later;   // kGroupWords words per later group
+};
+GroupPlan make_groups(const Tree& t);
+
+// Leaf record of a group of at most kGroupRanks ranks: its first rank and
+// (second word) the post-order offset of heap position h in bits
+// [3 (h - 1), 3 h) for h = 1..7 (unused positions: position 1's), n in bits
+// 21..23.
+uint32_t leaf_shape(int n);
+
+// Device table of a level work item: the leaf records (2 words each), padded
+// to a multiple of 4 words, then the later records.
+std::vector<uint32_t> group_table(const GroupPlan& g);
+inline size_t group_later_at(int g1) { return ((size_t)g1 * 2 + 3) & ~(size_t)3; }
+
 // Per-rank down-phase entries for the round-structured executor:
 // parent << 8 | depth, parent 0xFFFFFF for a root.  Needs p < 2^24, depth
 // < 256.
@@ -100,7 +141,8 @@ std::vector<uint32_t> make_depth_order(const Tree& t);
 // REDUCE_BCAST with H > 0).
 int device_rounds(const Tree& real, Alg alg, int b);
 
-// Ranks in level order for level-synchronous evaluation: deepest level
+// Ranks in level order (no kernel reads it; the tests replay it as an order
+// of their own beside the group plan): deepest level
 // first, ranks ascending within a level; entry = rank << 16 | code with code
 // 0xFFFF for a leaf, 0xFFFE for a rank whose only child is rank - 1, else the
 // second child's rank (the first is rank - 1).  The p entries are followed by
