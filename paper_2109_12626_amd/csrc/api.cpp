@@ -62,6 +62,9 @@ constexpr int kSubDeepMinRanks = 1024;
 constexpr int kWideFuseMaxRanks = 36;
 constexpr int kWideFuseTwoRanks = 20;
 constexpr int kWideFuseAnyRanks = 8;
+// Rows of at most dpar::kFewRanks ranks from which the register kernel takes
+// fused calls of more than one wide item per CU.
+constexpr uint64_t kFewRowBytes = 32ull << 20;
 // Wide work items from 3/4 of an item per CU on, from 7/8 with at most
 // kWideLateRanks ranks.
 constexpr int kWideLateRanks = 16;
@@ -1127,7 +1130,7 @@ const char* unit_name(dpar::Unit u) {
 void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
               dpar_alg_t alg, bool rule_b, const dpar::Schedule& s,
               dpar::Path path, dpar::Exec ex, dpar::Unit unit, int waves,
-              const dpar::Params& prm, int height) {
+              const dpar::Params& prm, int height, bool few) {
   static const char* dts[] = {"int32", "float32", "u32mat2x2"};
   static const char* opn[] = {"sum", "max", "matmul"};
   static const char* algs[] = {"dual_root", "single_tree", "reduce_bcast"};
@@ -1150,6 +1153,7 @@ void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
   if (unit == dpar::Unit::WIDE)
     std::fprintf(stderr, " full_items=%u", prm.wide_full);
   if (ex == dpar::Exec::TICKET) std::fprintf(stderr, " batch=%u", prm.batch);
+  if (few) std::fprintf(stderr, " in_registers");
   std::fprintf(stderr, "\n");
 }
 
@@ -1653,9 +1657,24 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
     prm.xcd_runs = 1;
   if (up == dpar::Exec::SPLIT || prm.flat)
     prm.xcd_runs = env_int("DPAR_XCD_RUNS", prm.xcd_runs) != 0;
+  // AUTO, fused, at most kFewRanks ranks on 16-byte lanes: the kernel that
+  // holds all rows in registers (kernels.hip k_few), except on rows of more
+  // than one wide item per CU and less than kFewRowBytes, where the wide items
+  // are faster (p = 8, m = 2^21 / 2^22: 21.2 / 47.2 us wide, 25.2 / 47.7 us;
+  // p = 2, m = 2^22 10.4 and 12.4 us; m = 2^20, one item per CU: p = 8 12.8
+  // and 11.5 us; rows of 32 MB: p = 8 96.6 and 95.4 us, p = 3 35.1 and
+  // 34.4 us; of 64 MB: p = 4 93.6 and 90.8 us, p = 2 45.6 and 44.3 us).  A
+  // forced work item (DPAR_UNIT) is run as asked.
+  const char* unit_env = std::getenv("DPAR_UNIT");
+  const bool few = exec == DPAR_EXEC_AUTO && up == dpar::Exec::DISPATCH &&
+                   p <= dpar::kFewRanks && path == dpar::Path::VEC16 &&
+                   !(unit_env && *unit_env) &&
+                   (wide_n <= ncu || (uint64_t)m * esz >= kFewRowBytes);
+  // (its trailing elements are its own: not the level item's)
+  if (few) tail = s.tail;
   if (env_int("DPAR_LOG", 0) != 0)
     log_plan(p, m, dtype, op, alg, rule_b, s, path, up, uc.unit, waves, prm,
-             ops->real_height);
+             ops->real_height, few);
   // The cooperative executors start from zeroed barrier words (arrivals,
   // generation, give-up): a call whose wait gave up may leave them out of
   // step, and its counter slot comes round again kCounterSlots calls later.
@@ -1665,8 +1684,20 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
         hipMemsetAsync(line, 0, kCounterStride * sizeof(unsigned), stream);
     if (ez != hipSuccess) return hip_fail(ez, "hipMemsetAsync barrier words");
   }
-  hipError_t e = dpar::launch(kind, path, unit, waves, up, tab, prm, stream,
-                              st->num_cus, lds_floor);
+  hipError_t e;
+  if (few) {
+    dpar::FewRun f{x, y, p, single, s.Q, 0};
+    // trailing elements ride in the last run of quanta, as above
+    if (tail > 0 && s.Q % (64 * dpar::kFewQ) != 0) {
+      f.Q = s.Q + 1;
+      f.over = (uint32_t)(4 - tail) * 4;
+      tail = 0;
+    }
+    e = dpar::launch_few(kind, f, stream);
+  } else {
+    e = dpar::launch(kind, path, unit, waves, up, tab, prm, stream,
+                     st->num_cus, lds_floor);
+  }
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   if (tail > 0) {
     // the elements after the last whole 16-byte quantum: one more chunk of

@@ -975,6 +975,88 @@ __device__ __forceinline__ void run_wide_item(const WideArgs& a, uint64_t t,
         slots);
 }
 
+// ------------------------------------------------------------ few ranks
+// One fused launch of at most kFewRanks ranks: a lane loads kFewQ quanta of
+// every row at once, combines them in registers in the trees' order, which is
+// known when the kernel is compiled, and writes y to every row.  No LDS, no
+// tables: the row addresses come in the kernel arguments, so a short call
+// waits for one trip to memory instead of three (p = 8, m = 2^18 fp32 5.6 ->
+// 4.7 us, m = 2^20 12.8 -> 11.5 us; p = 5, m = 2^20 8.4 -> 7.0 us), and a long
+// one, bound by HBM with both directions in one launch, has all its reads in
+// flight (p = 8, m = 2^24, 1.07 GB: 194.6 -> 184.4 us, 5.8 TB/s; one or four
+// quanta per lane 230 and 193 us).
+
+// A heap-shaped tree of n nodes in post-order (left subtree, right subtree,
+// node): nodes below and at heap position h, first rank of that subtree.
+constexpr int heap_size(int n, int h) {
+  return h > n ? 0 : 1 + heap_size(n, 2 * h) + heap_size(n, 2 * h + 1);
+}
+constexpr int heap_first(int n, int h) {
+  return h == 1       ? 0
+         : h % 2 == 0 ? heap_first(n, h / 2)
+                      : heap_first(n, h / 2) + heap_size(n, h - 1);
+}
+
+// The value of heap position H of the tree of N ranks whose blocks are
+// v[R0 .. R0 + N - 1]: the first child's value (2 H + 1, or 2 H when it is the
+// only one), then the second's.
+template <class L, int R0, int N, int H, int P>
+__device__ __forceinline__ typename L::T heap_value(
+    const typename L::T (&v)[P]) {
+  constexpr int at = R0 + heap_first(N, H) + heap_size(N, H) - 1;
+  typename L::T r = v[at];
+  if constexpr (2 * H + 1 <= N)
+    r = L::ap(heap_value<L, R0, N, 2 * H + 1>(v), r);
+  if constexpr (2 * H <= N) r = L::ap(heap_value<L, R0, N, 2 * H>(v), r);
+  return r;
+}
+
+template <int P>
+struct FewArgs {
+  uint64_t x[P], y[P];
+  uint64_t Q;      // quanta, an overlapping last one included
+  uint32_t over;   // bytes by which the last quantum starts early
+};
+
+// ONE: a single tree over the ranks, else the two dual-root trees.
+template <class L, int P, bool ONE>
+__global__ __launch_bounds__(256) void k_few(FewArgs<P> a, uint64_t first) {
+  using T = typename L::T;
+  constexpr int Q = kFewQ;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint64_t q0 = ((first + blockIdx.x) * 4 + wave) * (64 * Q);
+  if (q0 >= a.Q) return;  // wave-uniform
+  const uint32_t count = (uint32_t)min((uint64_t)64 * Q, a.Q - q0);
+  const uint64_t base = q0 * L::bytes;
+  uint32_t off[Q];
+  T v[Q][P];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    const uint32_t q = min((uint32_t)lane + 64u * u, count - 1);
+    off[u] = q * L::bytes - (q0 + q + 1 == a.Q ? a.over : 0u);
+  }
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int u = 0; u < Q; ++u) v[u][i] = L::load(a.x[i] + base, off[u]);
+  T y[Q];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    if constexpr (ONE)
+      y[u] = heap_value<L, 0, P, 1>(v[u]);
+    else
+      y[u] = L::ap(heap_value<L, 0, (P + 1) / 2, 1>(v[u]),
+                   heap_value<L, (P + 1) / 2, P / 2, 1>(v[u]));
+  }
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int u = 0; u < Q; ++u)
+      if ((uint32_t)lane + 64u * u < count)
+        L::store(a.y[i] + base, off[u], y[u]);
+}
+
 // ------------------------------------------------------------ unit policies
 
 template <class L, int W, bool FUSED>
@@ -1547,6 +1629,37 @@ hipError_t launch_wide(Exec exec, const Tables& tab, const Params& prm,
   return launch_ticket<U>(tab, prm, stream, num_cus, lds, per_cu);
 }
 
+template <class L, int P, bool ONE>
+hipError_t launch_few_t(const FewRun& f, hipStream_t stream) {
+  FewArgs<P> a{};
+  for (int i = 0; i < P; ++i) {
+    a.x[i] = (uint64_t)(uintptr_t)f.x[i];
+    a.y[i] = (uint64_t)(uintptr_t)f.y[i];
+  }
+  a.Q = f.Q;
+  a.over = f.over;
+  const uint64_t kMaxGrid = (1ull << 31) / 256;  // threads per launch < 2^32
+  const uint64_t items = (f.Q + 256 * kFewQ - 1) / (256 * kFewQ);
+  for (uint64_t first = 0; first < items; first += kMaxGrid)
+    hipLaunchKernelGGL((k_few<L, P, ONE>),
+                       dim3((unsigned)min(kMaxGrid, items - first)), dim3(256),
+                       0, stream, a, first);
+  return hipGetLastError();
+}
+
+template <class L, int P>
+hipError_t launch_few_p(const FewRun& f, hipStream_t stream) {
+  if constexpr (P > kFewRanks) {
+    return hipErrorInvalidValue;
+  } else {
+    if (f.p != P) return launch_few_p<L, P + 1>(f, stream);
+    // (the two layouts give the same product of two ranks)
+    if constexpr (P > 2)
+      if (f.one_tree) return launch_few_t<L, P, true>(f, stream);
+    return launch_few_t<L, P, false>(f, stream);
+  }
+}
+
 template <class L>
 hipError_t launch_l(Unit unit, int waves, Exec exec, const Tables& tab,
                     const Params& prm, hipStream_t stream, int num_cus,
@@ -1620,6 +1733,16 @@ hipError_t launch(Kind kind, Path path, Unit unit, int waves, Exec exec,
       return DPAR_LAUNCH_L(LaneMat);  // 16-byte lanes on either path
   }
 #undef DPAR_LAUNCH_L
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_few(Kind kind, const FewRun& f, hipStream_t stream) {
+  switch (kind) {
+    case Kind::I32_SUM: return launch_few_p<Lane4<I32Sum>, 2>(f, stream);
+    case Kind::I32_MAX: return launch_few_p<Lane4<I32Max>, 2>(f, stream);
+    case Kind::F32_SUM: return launch_few_p<Lane4<F32Sum>, 2>(f, stream);
+    case Kind::MAT: return launch_few_p<LaneMatLv, 2>(f, stream);
+  }
   return hipErrorInvalidValue;
 }
 

@@ -126,6 +126,22 @@ hipError_t launch(Kind kind, Path path, Unit unit, int waves, Exec exec,
                   const Tables& tab, const Params& prm, hipStream_t stream,
                   int num_cus, size_t lds_floor);
 
+// One fused launch of 2 .. kFewRanks ranks on 16-byte lanes, rows in host
+// arrays: Q quanta from the rows' first element, the last one `over` bytes
+// early (then both it and the one before must be in one run of 64 kFewQ
+// quanta, which a wavefront loads before it writes).
+constexpr int kFewRanks = 8;
+constexpr int kFewQ = 2;
+struct FewRun {
+  const void* const* x;
+  void* const* y;
+  int p;
+  bool one_tree;
+  uint64_t Q;
+  uint32_t over;
+};
+hipError_t launch_few(Kind kind, const FewRun& f, hipStream_t stream);
+
 // LDS a work item's dynamic request must leave free for the kernels' own
 // static LDS (the ticket executor's claim word): the host compares
 // requests with the device limit minus this.  (A subtree plan needing
