@@ -1216,10 +1216,58 @@ __global__ __launch_bounds__(U::kThreads) void k_barrier(DPAR_KARGS) {
 // schedule of Algorithm 1; dshift = b - 1: the broadcast that follows a
 // completed reduction, Section 2's reduce-then-broadcast).
 
+// One rank's share of a down-step piece: up to kDownPiece quanta of the block
+// it receives this round, from its parent's output row to its own (n = 0:
+// nothing to receive).
+struct DownPart {
+  uint64_t src, dst;  // the piece's first byte in the two rows
+  uint32_t par;
+  uint32_t n;         // quanta
+};
+template <class L>
+__device__ __forceinline__ DownPart down_part(const uint64_t* __restrict__ yp,
+                                              uint32_t i, uint32_t e,
+                                              const Params& prm, int round,
+                                              uint64_t k) {
+  DownPart d{0, 0, e >> 8, 0};
+  const int64_t j = (int64_t)round - (int64_t)(e & 0xFFu) - prm.dshift;
+  if (d.par == 0xFFFFFFu || j < 0 || j >= prm.b) return d;  // not in range
+  const uint64_t ls = prm.NL * (uint64_t)j / (uint64_t)prm.b;
+  const uint64_t le = prm.NL * (uint64_t)(j + 1) / (uint64_t)prm.b;
+  const uint64_t ps = min(ls * prm.lq, prm.Q) + k * kDownPiece;
+  const uint64_t qe = min(le * prm.lq, prm.Q);
+  if (ps >= qe) return d;
+  const uint64_t off = (prm.qbase + ps) * L::bytes;
+  d.src = yp[d.par] + off;
+  d.dst = yp[i] + off;
+  d.n = (uint32_t)min((uint64_t)kDownPiece, qe - ps);
+  return d;
+}
+
+// A store whose line stays in the caches (lane type T, 4-byte aligned).
+template <class T>
+__device__ __forceinline__ void store_kept(uint64_t row, uint32_t off, T v) {
+  using G = std::conditional_t<sizeof(T) == 16, u32x4g, T>;
+  *gptr_w<G>(row, off) = v;
+}
+
 // Down-step for the ranks at positions [a0, a1) of the depth-ordered rank
-// table, piece k (kDownPiece quanta) of their blocks: the workgroup's
-// wavefronts take the ranks in turn; a lane copies 4 quanta, all loads in
-// flight before the stores.
+// table, piece k (kDownPiece quanta) of their blocks: each wavefront takes two
+// neighbouring ranks, a lane copies kDownPiece / 64 quanta of each, all loads
+// in flight before the stores.
+//
+// Bound by memory traffic (a rank's block is read from its parent's row and
+// written to its own) and, in short rounds, by the wait on the loads.  Two
+// children of one parent are neighbours in the table and receive the same
+// block in the same round: it is read once and written twice.  The stores are
+// ordinary ones, unlike the other kernels': the next round reads what they
+// write.  Pieces of 128 quanta leave twice the wavefronts of 256 to overlap
+// with the round's up-step; 64 gain nothing more.  int32 SUM, one MI355X, one
+// launch per round, each rank on its own with a streaming store / shared reads
+// / ordinary stores as well / with 128 quanta: p = 288, m = 250000, b = 16 321
+// / 289 / 276 / 268 us; p = 64, m = 1500000, b = 94 901 / 746 / 712 / 680 us;
+// p = 1152, m = 65536 fp32, b = 5 329 / 228 / 214 / 208 us; matrices, p = 120,
+// m = 200001, b = 13 351 / 314 / 309 / 316 us.
 template <class L, int TH>
 __device__ __forceinline__ void down_copy(const uint64_t* __restrict__ yp,
                                           const uint32_t* __restrict__ dn,
@@ -1229,32 +1277,47 @@ __device__ __forceinline__ void down_copy(const uint64_t* __restrict__ yp,
                                           uint64_t k) {
   constexpr int kWaves = TH / 64;
   constexpr int kQ = kDownPiece / 64;
-  const int lane = threadIdx.x & 63;
+  const uint32_t lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  for (uint32_t a = a0 + wave; a < a1; a += kWaves) {
-    const uint32_t i = ranks[a];
-    const uint32_t e = dn[i];
-    const uint32_t par = e >> 8;
-    const int64_t j = (int64_t)round - (int64_t)(e & 0xFFu) - prm.dshift;
-    if (par == 0xFFFFFFu || j < 0 || j >= prm.b) continue;  // not in range
-    const uint64_t ls = prm.NL * (uint64_t)j / (uint64_t)prm.b;
-    const uint64_t le = prm.NL * (uint64_t)(j + 1) / (uint64_t)prm.b;
-    const uint64_t qs = min(ls * prm.lq, prm.Q);
-    const uint64_t qe = min(le * prm.lq, prm.Q);
-    const uint64_t ps = qs + k * kDownPiece;
-    if (ps >= qe) continue;
-    const uint64_t src = yp[par] + prm.qbase * L::bytes;
-    const uint64_t dst = yp[i] + prm.qbase * L::bytes;
-    typename L::T v[kQ];
+  for (uint32_t a = a0 + 2 * wave; a < a1; a += 2 * kWaves) {
+    const bool two = a + 1 < a1;
+    const uint32_t i0 = ranks[a], i1 = ranks[two ? a + 1 : a];
+    const uint32_t e0 = dn[i0], e1 = dn[i1];
+    const DownPart d0 = down_part<L>(yp, i0, e0, prm, round, k);
+    if (e1 == e0) {  // siblings (or one rank alone): one parent, one block
+      const uint64_t dst1 = yp[i1] + (d0.dst - yp[i0]);
+      typename L::T v[kQ];
+#pragma unroll
+      for (int u = 0; u < kQ; ++u)
+        if (lane + 64u * u < d0.n)
+          v[u] = L::load(d0.src, (lane + 64u * u) * L::bytes);
+#pragma unroll
+      for (int u = 0; u < kQ; ++u)
+        if (lane + 64u * u < d0.n)
+          store_kept<typename L::T>(d0.dst, (lane + 64u * u) * L::bytes, v[u]);
+      if (two) {
+#pragma unroll
+        for (int u = 0; u < kQ; ++u)
+          if (lane + 64u * u < d0.n)
+            store_kept<typename L::T>(dst1, (lane + 64u * u) * L::bytes, v[u]);
+      }
+      continue;
+    }
+    const DownPart d1 = down_part<L>(yp, i1, e1, prm, round, k);
+    typename L::T v[kQ], w[kQ];
 #pragma unroll
     for (int u = 0; u < kQ; ++u) {
-      const uint64_t q = ps + (uint64_t)u * 64 + lane;
-      if (q < qe) v[u] = L::load(src + q * L::bytes, 0);
+      if (lane + 64u * u < d0.n)
+        v[u] = L::load(d0.src, (lane + 64u * u) * L::bytes);
+      if (lane + 64u * u < d1.n)
+        w[u] = L::load(d1.src, (lane + 64u * u) * L::bytes);
     }
 #pragma unroll
     for (int u = 0; u < kQ; ++u) {
-      const uint64_t q = ps + (uint64_t)u * 64 + lane;
-      if (q < qe) L::store(dst + q * L::bytes, 0, v[u]);
+      if (lane + 64u * u < d0.n)
+        store_kept<typename L::T>(d0.dst, (lane + 64u * u) * L::bytes, v[u]);
+      if (lane + 64u * u < d1.n)
+        store_kept<typename L::T>(d1.dst, (lane + 64u * u) * L::bytes, w[u]);
     }
   }
 }

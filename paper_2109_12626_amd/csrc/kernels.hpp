@@ -94,8 +94,8 @@ struct Params {
                         // the full items)
 };
 
-// Quanta per down-step piece: 64 lanes x 4 quanta per lane.
-constexpr int kDownPiece = 256;
+// Quanta per down-step piece: 64 lanes x 2 quanta per lane.
+constexpr int kDownPiece = 128;
 
 // Ticket counters per call (each on its own 128-byte line): work-item batch
 // k belongs to counter k % kTicketCounters, which spreads the atomics.
