@@ -13,8 +13,8 @@ enum class Kind : int { I32_SUM = 0, I32_MAX = 1, F32_SUM = 2, MAT = 3 };
 // SCALAR: one 4-byte scalar (or one matrix read as 4 dwords) per lane.
 enum class Path : int { VEC16 = 0, SCALAR = 1 };
 // How one work item (a chunk of a block) is evaluated: a post-order walk per
-// wavefront over 16-byte lanes (SEQ) or level by level with the whole chunk
-// staged in LDS (LEVEL; short chunks, latency-bound cases).
+// wavefront over 16-byte lanes (SEQ) or in groups of at most 7 ranks, three
+// tree levels per step (LEVEL; short chunks, latency-bound cases).
 // SUB: the trees cut into subtrees, one wavefront each, then the spines
 // (few chunks, large p).  WIDE: the post-order walk with kWideQ quanta per
 // lane and kWideWaves wavefronts on neighbouring columns (few ranks, long
