@@ -102,24 +102,30 @@ struct F32Sum {
   }
 };
 
-// 2x2 matrix product mod 2^32, row-major [a00, a01, a10, a11]; a on the left.
-__device__ inline u32x4 mat_mul(u32x4 a, u32x4 b) {
-  u32x4 c;
-  c.x = a.x * b.x + a.y * b.z;
-  c.y = a.x * b.y + a.y * b.w;
-  c.z = a.z * b.x + a.w * b.z;
-  c.w = a.z * b.y + a.w * b.w;
-  return c;
-}
-
-// a b + c d mod 2^32, each product a 32-bit multiply of its own (the empty asm
-// hides where it comes from).
+// a b + c d mod 2^32, each product a 32-bit multiply of its own: the empty asm
+// keeps the compiler from merging a product and the addition into a
+// 32 x 32 + 64-bit multiply-add (v_mad_u64_u32), of which only the low half is
+// wanted.  With merged ones, and products under uniform branches, clang 22
+// (ROCm 7.2.0) gave a level item in which the high half of entry 0 overwrote
+// entry 1: the register pair v[32:33] was the multiply-add's destination,
+// entry 1 stayed in v36, and v[32:35] was stored.  Every matrix kernel takes
+// its products under such branches.
 __device__ inline uint32_t dot2(uint32_t a, uint32_t b, uint32_t c,
                                 uint32_t d) {
   uint32_t u = a * b, v = c * d;
   asm("" : "+v"(u));
   asm("" : "+v"(v));
   return u + v;
+}
+
+// 2x2 matrix product mod 2^32, row-major [a00, a01, a10, a11]; a on the left.
+__device__ inline u32x4 mat_mul(u32x4 a, u32x4 b) {
+  u32x4 c;
+  c.x = dot2(a.x, b.x, a.y, b.z);
+  c.y = dot2(a.x, b.y, a.y, b.w);
+  c.z = dot2(a.z, b.x, a.w, b.z);
+  c.w = dot2(a.z, b.y, a.w, b.w);
+  return c;
 }
 
 // ------------------------------------------------------------ lane layouts
@@ -168,30 +174,6 @@ struct LaneMat {  // one matrix, one 16-byte access (4-byte aligned)
   __device__ static void store(uint64_t row, uint32_t off, T v) {
     st(gptr_w<u32x4g>(row, off), (u32x4g)v);
   }
-};
-
-// The matrix lane of the level work item.  Left to itself the compiler merges
-// a product and the addition into a 32 x 32 + 64-bit multiply-add; with the
-// products under uniform branches (a wavefront per group) it then kept the
-// multiply-add's high half in place of a neighbouring entry: wrong matrices
-// from 3 ranks on.
-struct LaneMatLv : LaneMat {
-  __device__ static T ap(T a, T b) {
-    T c;
-    c.x = dot2(a.x, b.x, a.y, b.z);
-    c.y = dot2(a.x, b.y, a.y, b.w);
-    c.z = dot2(a.z, b.x, a.w, b.z);
-    c.w = dot2(a.z, b.y, a.w, b.w);
-    return c;
-  }
-};
-template <class L>
-struct LevelLane {
-  using type = L;
-};
-template <>
-struct LevelLane<LaneMat> {
-  using type = LaneMatLv;
 };
 
 // ------------------------------------------------------------ one work item
@@ -1734,19 +1716,18 @@ hipError_t launch_l(Unit unit, int waves, Exec exec, const Tables& tab,
                                              : exec;
 #define DPAR_LAUNCH_U(...) \
   launch_u<__VA_ARGS__>(ex, tab, prm, stream, num_cus, lds_floor)
-  using LL = typename LevelLane<L>::type;
   if (unit == Unit::LEVEL && ex == Exec::DISPATCH && prm.lv_log2t == 6) {
     // 1 KB (or 256-byte) chunks: a wavefront per group
     const unsigned th = (unsigned)prm.lv_threads;
-    const size_t lds = LvUnit<LL, true, true>::lds(prm);
-    return fused ? launch_items<LvUnit<LL, true, true>>(tab, prm, stream, th,
-                                                       lds)
-                 : launch_items<LvUnit<LL, false, true>>(tab, prm, stream, th,
-                                                        lds);
+    const size_t lds = LvUnit<L, true, true>::lds(prm);
+    return fused ? launch_items<LvUnit<L, true, true>>(tab, prm, stream, th,
+                                                      lds)
+                 : launch_items<LvUnit<L, false, true>>(tab, prm, stream, th,
+                                                       lds);
   }
   if (unit == Unit::LEVEL)
-    return fused ? DPAR_LAUNCH_U(LvUnit<LL, true>)
-                 : DPAR_LAUNCH_U(LvUnit<LL, false>);
+    return fused ? DPAR_LAUNCH_U(LvUnit<L, true>)
+                 : DPAR_LAUNCH_U(LvUnit<L, false>);
   if (unit == Unit::SUB) {
     if (prm.sub_deep)
       return fused ? DPAR_LAUNCH_U(SubUnit<L, true, kUDeep>)
@@ -1804,7 +1785,7 @@ hipError_t launch_few(Kind kind, const FewRun& f, hipStream_t stream) {
     case Kind::I32_SUM: return launch_few_p<Lane4<I32Sum>, 2>(f, stream);
     case Kind::I32_MAX: return launch_few_p<Lane4<I32Max>, 2>(f, stream);
     case Kind::F32_SUM: return launch_few_p<Lane4<F32Sum>, 2>(f, stream);
-    case Kind::MAT: return launch_few_p<LaneMatLv, 2>(f, stream);
+    case Kind::MAT: return launch_few_p<LaneMat, 2>(f, stream);
   }
   return hipErrorInvalidValue;
 }
