@@ -13,6 +13,8 @@
 #include <string>
 #include <vector>
 
+#include <unistd.h>
+
 #include "dpar.h"
 #include "kernels.hpp"
 #include "plan.hpp"
@@ -214,6 +216,23 @@ FixedState g_fixed[kFixedMaxDevices];
 int env_int(const char* name, int dflt) {
   const char* v = std::getenv(name);
   return v && *v ? std::atoi(v) : dflt;
+}
+
+// Whether one of the switches that pick or shape a work item is set: such a
+// call runs the work item it would run without the few-rank kernel.  One pass
+// over the environment, which short calls take on every call.
+bool item_switch_set() {
+  static const char* const names[] = {"UNIT=", "WAVES=", "WIDE_TAIL=",
+                                      "WIDE_ROUND=", "LEVEL_LOG2T="};
+  for (char* const* e = environ; e && *e; ++e) {
+    const char* v = *e;
+    if (v[0] != 'D' || std::strncmp(v, "DPAR_", 5) != 0) continue;
+    for (const char* n : names) {
+      const size_t len = std::strlen(n);
+      if (std::strncmp(v + 5, n, len) == 0 && v[5 + len]) return true;
+    }
+  }
+  return false;
 }
 
 unsigned long long spin_limit() {
@@ -1064,7 +1083,9 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   if (forced) want_sub = !std::strcmp(u, "sub") && sub_fits;
   if (want_sub) {
     uc.unit = dpar::Unit::SUB;
-    uc.grouped = one_pass && !forced && ops.lvl &&
+    // (DPAR_SUB_DEEP is about the walks: set, they run)
+    const char* deep = std::getenv("DPAR_SUB_DEEP");
+    uc.grouped = one_pass && !forced && ops.lvl && !(deep && *deep) &&
                  (lane_bytes << flat_lt) >= kLvMinPiece;
     uc.lv_log2t = flat_lt;
     return uc;
@@ -1664,12 +1685,11 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // p = 2, m = 2^22 10.4 and 12.4 us; m = 2^20, one item per CU: p = 8 12.8
   // and 11.5 us; rows of 32 MB: p = 8 96.6 and 95.4 us, p = 3 35.1 and
   // 34.4 us; of 64 MB: p = 4 93.6 and 90.8 us, p = 2 45.6 and 44.3 us).  A
-  // forced work item (DPAR_UNIT) is run as asked.
-  const char* unit_env = std::getenv("DPAR_UNIT");
+  // work item that a switch picks or shapes is run as asked.
   const bool few = exec == DPAR_EXEC_AUTO && up == dpar::Exec::DISPATCH &&
                    p <= dpar::kFewRanks && path == dpar::Path::VEC16 &&
-                   !(unit_env && *unit_env) &&
-                   (wide_n <= ncu || (uint64_t)m * esz >= kFewRowBytes);
+                   (wide_n <= ncu || (uint64_t)m * esz >= kFewRowBytes) &&
+                   !item_switch_set();
   // (its trailing elements are its own: not the level item's)
   if (few) tail = s.tail;
   if (env_int("DPAR_LOG", 0) != 0)
