@@ -400,8 +400,11 @@ const char* dpar_last_error(void);
  *   DPAR_SPIN_LIMIT=n       grid-barrier watchdog, in polls (default 2^26)
  *   DPAR_LOG=1              print each call's plan on stderr: p, m, dtype,
  *                           operator, algorithm, tree height H, b, lane
- *                           width, decomposition, executor, work-item kind,
- *                           work items */
+ *                           width, decomposition, executor, work-item kind
+ *                           (unit=), work items, the kernel that runs
+ *                           (kernel=: subtree calls of SPLIT and of fused
+ *                           launches run level items, fused calls of at most
+ *                           8 ranks the register kernel) */
 
 /* Frees every library-owned device and pinned host buffer (device tables,
  * counters, staging).  The library re-creates them lazily on the next call.

@@ -1148,10 +1148,13 @@ const char* unit_name(dpar::Unit u) {
 
 // DPAR_LOG=1: one line per call on stderr with the plan it runs (tree
 // height, block count, decomposition, executor, work item), for diagnosis.
+// unit= is the work item that the rules above name, kernel= the one that runs:
+// subtree calls of one pass run level items over whole chunks, and fused calls
+// of few ranks the register kernel.
 void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
               dpar_alg_t alg, bool rule_b, const dpar::Schedule& s,
-              dpar::Path path, dpar::Exec ex, dpar::Unit unit, int waves,
-              const dpar::Params& prm, int height, bool few) {
+              dpar::Path path, dpar::Exec ex, dpar::Unit unit, dpar::Unit run,
+              int waves, const dpar::Params& prm, int height, bool few) {
   static const char* dts[] = {"int32", "float32", "u32mat2x2"};
   static const char* opn[] = {"sum", "max", "matmul"};
   static const char* algs[] = {"dual_root", "single_tree", "reduce_bcast"};
@@ -1166,7 +1169,7 @@ void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
                path == dpar::Path::VEC16 ? "16B" : "4B", s.g, s.lq,
                (unsigned long long)s.tail, exec_name(ex), unit_name(unit),
                waves, prm.C, prm.grp, (unsigned long long)items);
-  if (unit == dpar::Unit::LEVEL || prm.flat)
+  if (run == dpar::Unit::LEVEL)
     std::fprintf(stderr, " level_chunk_quanta=%d threads=%d",
                  1 << prm.lv_log2t, prm.lv_threads);
   else if (unit == dpar::Unit::SUB)
@@ -1175,7 +1178,7 @@ void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
     std::fprintf(stderr, " full_items=%u", prm.wide_full);
   if (ex == dpar::Exec::TICKET) std::fprintf(stderr, " batch=%u", prm.batch);
   if (few) std::fprintf(stderr, " in_registers");
-  std::fprintf(stderr, "\n");
+  std::fprintf(stderr, " kernel=%s\n", few ? "few_ranks" : unit_name(run));
 }
 
 void set_groups(dpar::Params* prm, const GroupInts& g) {
@@ -1693,8 +1696,8 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // (its trailing elements are its own: not the level item's)
   if (few) tail = s.tail;
   if (env_int("DPAR_LOG", 0) != 0)
-    log_plan(p, m, dtype, op, alg, rule_b, s, path, up, uc.unit, waves, prm,
-             ops->real_height, few);
+    log_plan(p, m, dtype, op, alg, rule_b, s, path, up, uc.unit, unit, waves,
+             prm, ops->real_height, few);
   // The cooperative executors start from zeroed barrier words (arrivals,
   // generation, give-up): a call whose wait gave up may leave them out of
   // step, and its counter slot comes round again kCounterSlots calls later.
