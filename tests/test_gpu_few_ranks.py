@@ -32,12 +32,18 @@ def test_every_tree(p, alg, dtype, op, capfd):
     dpar = lib()
     words = 4 if dtype == "u32mat2x2" else 1
     s = torch.cuda.current_stream()
-    # quanta: 1, 127, 128, 129, 512, 513; then 4 m' + 1 .. 3 elements whose
-    # last quantum shares a run of 128 or not (more than 24 MB moved, below
-    # which such calls take one element per lane)
+    # quanta: 1, 127, 128, 129, 512, 513; then 4 m' + 1 .. 3 elements (more than
+    # 24 MB moved, below which such calls take one element per lane): whole
+    # quanta that fill their last run of 128, so that the trailing elements
+    # are a launch of their own, and that leave 1, 64 or 127 in it, so that
+    # they ride there as a quantum that overlaps the one before
     sizes = [4, 508, 512, 516, 2048, 2052]
-    if words == 1 and p == 8 and alg == "dual":
-        sizes += [400385, 399874, 399875, 399361]
+    if words == 1 and p == 8 and alg != "reduce_bcast":
+        full = [400385, 399874, 399875, 399361]
+        rides = [4 * 100097 + 1, 4 * 100160 + 2, 4 * 100095 + 3]
+        assert [m // 4 % 128 for m in full] == [0] * 4
+        assert [m // 4 % 128 for m in rides] == [1, 64, 127]
+        sizes += full + rides
     for m in sizes:
         x = _data(dtype, p, m)
         want = c_oracle.allreduce(x, dtype, op,
