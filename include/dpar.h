@@ -235,7 +235,7 @@ int dpar_allreduce(const void* const* x, void* const* y, int p, size_t m,
  * call hipMalloc, e.g. tight serving loops or harnesses that forbid it): the
  * same computation, arguments, results and errors as dpar_allreduce, with
  * no device or pinned host allocation in the call.  The library's device
- * tables (opcodes, level table, subtree plan, the pointer tables) live in a
+ * tables (opcodes, group table, subtree plan, the pointer tables) live in a
  * fixed 1 MiB device array per GPU, held until the process ends; they are
  * written by small copy kernels whose data travels in kernel arguments,
  * only when p or the pointer arrays differ from the previous call of this

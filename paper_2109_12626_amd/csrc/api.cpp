@@ -198,7 +198,7 @@ std::map<int, std::unique_ptr<DeviceState>> g_devices;
 
 // The allocation-free entry point (dpar_allreduce_noalloc): per device, the
 // address of the library's fixed scratch array and what it holds.  Layout
-// for p ranks: opcode table | level table | subtree plan | pointer tables,
+// for p ranks: opcode table | group table | subtree plan | pointer tables,
 // each at a 256-byte boundary.
 constexpr int kFixedMaxDevices = 64;
 struct FixedState {
@@ -296,7 +296,7 @@ void free_ops(OpsTable& t) {
 }
 
 // Device tables for p ranks on the dual-root trees or on one tree: the
-// opcodes and level table of the form the kernels evaluate, and the real
+// opcodes and group table of the form the kernels evaluate, and the real
 // tree's parents and depths for the round-structured down-step.
 int get_ops(DeviceState* st, int p, bool single, const OpsTable** out) {
   const auto key = std::make_pair(p, single ? 1 : 0);
@@ -1737,7 +1737,7 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
     tp.batch = 1;
     tp.xcd_runs = 0;
     // at most 3 elements: evaluated level by level (all p loads at once)
-    // where the level table exists; a post-order walk would be a chain of
+    // where the group table exists; a post-order walk would be a chain of
     // p / 2 dependent loads (p = 288, 2125 elements: 47 us per call with
     // the walk)
     dpar::Tables tt = tab;

@@ -141,14 +141,6 @@ std::vector<uint32_t> make_depth_order(const Tree& t);
 // REDUCE_BCAST with H > 0).
 int device_rounds(const Tree& real, Alg alg, int b);
 
-// Ranks in level order (no kernel reads it; the tests replay it as an order
-// of their own beside the group plan): deepest level
-// first, ranks ascending within a level; entry = rank << 16 | code with code
-// 0xFFFF for a leaf, 0xFFFE for a rank whose only child is rank - 1, else the
-// second child's rank (the first is rank - 1).  The p entries are followed by
-// H + 2 level boundaries.  Needs p <= 65534.
-std::vector<uint32_t> make_levels(const Tree& t);
-
 // Rounds with a non-empty exchange for one rank (rank == -1: overall).
 int rank_rounds(const Tree& t, int b, int rank);
 

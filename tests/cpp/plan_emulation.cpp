@@ -1,5 +1,6 @@
 // Symbolic replay of the device work items' evaluation order, driven by the
-// same host tables the kernels receive (opcodes, level table, subtree plan).
+// same host tables the kernels receive (opcodes, subtree plan), and of the
+// trees level by level.
 // Test infrastructure: for each p read from stdin it prints, per tree layout,
 // the product each work item would form, as a string over x0..x{p-1};
 // tests/test_plan_emulation.py compares them with the oracle's trees.
@@ -47,20 +48,17 @@ static S seq(const Tree& t, const std::vector<uint32_t>& ops, int waves) {
   return ap(a.at(0), cb);
 }
 
+// The trees themselves, one depth level at a time from the deepest up: a
+// rank's children are the ones the tree names, its first child rank - 1.  (The
+// level work item's own table, the groups, is replayed by group_plan.cpp.)
 static S level(const Tree& t) {
-  const std::vector<uint32_t> lv = make_levels(t);
   std::vector<S> s(t.p);
   for (int i = 0; i < t.p; ++i) s[i] = x(i);
-  const int nlev = t.height + 1;
-  for (int l = 0; l < nlev; ++l) {
-    for (uint32_t k = lv[t.p + l]; k < lv[t.p + l + 1]; ++k) {
-      const uint32_t e = lv[k];
-      const int node = (int)(e >> 16);
-      const uint32_t code = e & 0xFFFFu;
-      S v = s[node];
-      if (code != 0xFFFFu) v = ap(s[node - 1], v);
-      if (code < 0xFFFEu) v = ap(s[code], v);
-      s[node] = v;
+  for (int d = t.height; d >= 0; --d) {
+    for (int i = 0; i < t.p; ++i) {
+      if (t.depth[i] != d) continue;
+      if (t.child0[i] >= 0) s[i] = ap(s[i - 1], s[i]);
+      if (t.child1[i] >= 0) s[i] = ap(s[t.child1[i]], s[i]);
     }
   }
   return t.p >= 2 ? ap(s[t.n_a - 1], s[t.p - 1]) : s[t.n_a - 1];

@@ -1,7 +1,7 @@
 """The device work items' evaluation order, replayed symbolically on the
 CPU from the library's own host tables (tests/cpp/plan_emulation.cpp links
-the library's planner: opcodes, level table, subtree plan), must form
-exactly the product the oracle's trees define:
+the library's planner: opcodes, subtree plan, and the trees level by level),
+must form exactly the product the oracle's trees define:
 S(i) = S(child1) (.) (S(child0) (.) x_i), y = S(root A) (.) S(root B) on the
 dual-root trees, y = S(p - 1) on one tree (Sections 1.1, 1.2)."""
 
