@@ -77,13 +77,19 @@ constexpr int kWideLateRanks = 16;
 constexpr int kLvSplitRanks = 1024;
 constexpr int kLvSplitManyRanks = 512;
 constexpr int kLvCrowdRanks = 2048;
-// Bytes of each row a level item reads at least (kLvMinPieceDeep from
-// kLvCrowdRanks ranks on): int32 SUM, p = 1152, m = 1024 (256 quanta) fused
-// with 32 / 64 / 128 / 256 bytes 11.0 / 9.7 / 11.1 / 16.0 us, p = 288,
-// m = 875 with 16 / 32 / 64 / 128 bytes 7.1 / 6.6 / 6.6 / 8.1 us; p = 2304,
-// m = 4096 with 64 / 128 bytes 27.5 / 22.0 us.
-constexpr size_t kLvMinPiece = 64;
-constexpr size_t kLvMinPieceDeep = 128;
+// A level item's chunk (level_log2t), as powers of two of quanta: where the
+// rule starts with 16-byte lanes and with 4-byte ones, and how many places
+// (leaf groups x quanta) it lets a workgroup start with.  A workgroup takes
+// its places in turns, so with many ranks a chunk longer than the call needs
+// costs more than short pieces that share lines.  One launch, hot, chunks of
+// 1 / 2 / 4 / 8 / 16 quanta: fp32, 4-byte lanes, p = 4608 (578 groups), m = 5
+// 10.8 / 11.1 / 11.3 / 14.0 / 21.6 us; p = 288 (38), m = 513 9.0 / 7.6 / 5.8 /
+// 5.3 / 5.8 us; matrices, p = 4608, m = 1 11.1 / 11.0 / 12.7 / 17.7 / 28.5 us,
+// m = 64 28.1 / 26.9 / 26.5 / 28.7 / 39.7 us.
+constexpr int kLvMinLog2T = 2;
+constexpr int kLvMinLog2T4 = 3;
+constexpr int kLvMinWork = 1024;
+constexpr int kLvMinWork4 = 512;
 // From this many ranks (up to 255) level items take one-launch calls of up to
 // one 1 KB chunk of each row per CU (post-order -> level, one fused launch:
 // p = 36, m = 65536 8.9 -> 6.1 us, p = 64 9.5 -> 7.6 us, p = 128 17.0 ->
@@ -921,11 +927,17 @@ struct UnitChoice {
   uint64_t lv_items = 0;  // LEVEL: items if chunks were staged row by row
 };
 
-// Quanta per chunk of a level item, as a power of two: the smallest chunk
-// that leaves at most one item per CU (items(l): how many there are with 2^l
-// quanta), between kLvMinPiece bytes of each row (kLvMinPieceDeep from
-// kLvCrowdRanks ranks on) and what fits in LDS, at most 64.
-// DPAR_LEVEL_LOG2T forces it.
+// Quanta per chunk of a level item, as a power of two: at most one item per
+// CU, from the few quanta that the constants above say to what fits in LDS, at
+// most 64 (items(l): how many items there are with 2^l quanta).  With 16-byte
+// lanes four quanta also while there are more items than an eighth of the
+// CUs, and from kLvCrowdRanks ranks on whole lines once items for half the CUs
+// remain (p = 4608, m = 4000 in chunks of 4 / 8 / 16 quanta 41.6 / 35.2 / 50.9
+// us, p = 2304, m = 8192 45.4 / 30.4 / 35.5 us; p = 1152, m = 4000 13.7 / 14.1 /
+// 17.9 us).  Pieces of less than 64 bytes (4-byte lanes) share their lines with
+// more items, so those grow from 5/8 of an item per CU on (p = 700, m = 1001,
+// 251 items of 4 quanta 11.1 us, 126 of 8 9.2 us; p = 1152, m = 513, 129 items
+// of 4 quanta 10.0 us, 65 of 8 11.1 us).  DPAR_LEVEL_LOG2T forces it.
 template <class F>
 int level_log2t(size_t lane_bytes, int p, int g1, const DeviceState& st,
                 F items) {
@@ -935,10 +947,18 @@ int level_log2t(size_t lane_bytes, int p, int g1, const DeviceState& st,
     --top;
   const int forced_lg = env_int("DPAR_LEVEL_LOG2T", -1);
   if (forced_lg >= 0) return std::min(forced_lg, top);
-  const size_t piece = p >= kLvCrowdRanks ? kLvMinPieceDeep : kLvMinPiece;
-  int lg = 0;
-  while (lg < top && (lane_bytes << lg) < piece) ++lg;
-  while (lg < top && items(lg) > (uint64_t)st.num_cus) ++lg;
+  const uint64_t cus = (uint64_t)st.num_cus;
+  const bool wide = lane_bytes == 16;
+  int lg = std::min(top, wide ? kLvMinLog2T : kLvMinLog2T4);
+  const int least = lg;
+  while (lg > 0 && g1 << lg > (wide ? kLvMinWork : kLvMinWork4)) --lg;
+  if (wide) {
+    while (lg < least && 8 * items(lg) > cus) ++lg;
+    if (p >= kLvCrowdRanks && lg < top && 2 * items(lg) >= cus) ++lg;
+  }
+  while (lg < top &&
+         items(lg) > ((lane_bytes << lg) < 64 ? 5 * cus / 8 : cus))
+    ++lg;
   return lg;
 }
 
@@ -1070,11 +1090,10 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
         uc.unit = dpar::Unit::LEVEL;
         uc.lv_items = lv_items;
         // the chunk itself
+        auto count = [&](int l) { return groups * chunks(l); };
         uc.lv_log2t = one_pass ? flat_lt
                                : level_log2t(lane_bytes, p, ops.lv.g1, st,
-                                             [&](int l) {
-                                               return groups * chunks(l);
-                                             });
+                                             count);
         uc.lv_C = (int)chunks(uc.lv_log2t);
         return uc;
       }
@@ -1083,10 +1102,13 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   if (forced) want_sub = !std::strcmp(u, "sub") && sub_fits;
   if (want_sub) {
     uc.unit = dpar::Unit::SUB;
-    // (DPAR_SUB_DEEP is about the walks: set, they run)
+    // (DPAR_SUB_DEEP is about the walks: set, they run; and so do they where
+    // 64 bytes of each row do not fit in LDS)
     const char* deep = std::getenv("DPAR_SUB_DEEP");
     uc.grouped = one_pass && !forced && ops.lvl && !(deep && *deep) &&
-                 (lane_bytes << flat_lt) >= kLvMinPiece;
+                 dpar::level_lds_bytes(lane_bytes, ops.lv.g1,
+                                       lane_bytes == 16 ? 2 : 4) <=
+                     (size_t)st.lds_limit - dpar::kStaticLdsReserve;
     uc.lv_log2t = flat_lt;
     return uc;
   }

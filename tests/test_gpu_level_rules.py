@@ -1,0 +1,67 @@
+"""Rules of the level work item, each at the sizes where it turns, shown by the
+plan line; bit for bit against the oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import c_oracle
+from tests._gpu import _Env, assert_all_ranks_equal, env_unit, lib, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(p, m, dtype, exec, b, pad, capfd):
+    dpar = lib()
+    words = 4 if dtype == "u32mat2x2" else 1
+    op = "matmul" if words == 4 else "sum"
+    r = np.random.default_rng(6100 + p)
+    if dtype == "float32":
+        x = r.standard_normal((p, m), np.float32)
+    elif words == 4:
+        x = r.integers(0, 1 << 32, (p, m, 4), dtype=np.uint32)
+    else:
+        x = r.integers(-1 << 31, 1 << 31, (p, m), dtype=np.int32)
+    flat = np.ascontiguousarray(x).view(np.int32).reshape(p, -1)
+    n = flat.shape[1]
+    big = torch.full((p, n + pad), -7, dtype=torch.int32, device="cuda")
+    big[:, :n] = torch.from_numpy(flat).cuda()
+    out = torch.full_like(big, -7)
+    s = torch.cuda.current_stream()
+    with env_unit(None), _Env("DPAR_LOG", 1):
+        dpar.dpar_allreduce_ex(dpar.rows(big), dpar.rows(out), p, m, dtype,
+                               op, b, exec, s)
+    dpar.dpar_check_status(s)
+    err = capfd.readouterr().err
+    got = out.cpu().numpy()
+    assert (got[:, n:] == -7).all()
+    got = np.ascontiguousarray(got[:, :n]).view(x.dtype).reshape(x.shape)
+    want = c_oracle.allreduce(x, dtype, op, layout="dual", threads=8)
+    assert_all_ranks_equal(got, want, f"{p} {m} {dtype} {exec}")
+    return err
+
+
+# 4-byte lanes: one turn of 512 places, at most 8 quanta; then longer chunks
+# from 160 items on; 16-byte lanes: one turn of 1024 places, 4 quanta with more
+# items than an eighth of the CUs, whole lines from half an item per CU on
+@pytest.mark.parametrize("p,m,dtype,exec,quanta", [
+    (64, 33, "float32", "auto", 8),
+    (288, 1, "float32", "auto", 8),
+    (1152, 33, "int32", "auto", 2),
+    (4608, 7, "float32", "auto", 1),
+    (4608, 161, "float32", "auto", 2),
+    (6000, 5, "float32", "split", 1),
+    (4608, 3, "u32mat2x2", "auto", 1),
+    (4608, 33, "u32mat2x2", "auto", 2),
+    (4608, 65, "u32mat2x2", "auto", 4),
+    (2304, 512, "u32mat2x2", "auto", 8),
+    (2304, 508, "u32mat2x2", "auto", 4),
+    (1152, 1024, "u32mat2x2", "auto", 4),
+    (4608, 27, "u32mat2x2", "launch", 1),
+    (2304, 217, "float32", "rounds", 2),
+    (2304, 13, "int32", "ticket", 1),
+])
+def test_chunk(p, m, dtype, exec, quanta, capfd):
+    need_gpu()
+    err = _call(p, m, dtype, exec, 1, 0, capfd)
+    assert f" level_chunk_quanta={quanta} " in err, err
