@@ -90,6 +90,16 @@ constexpr int kLvMinLog2T = 2;
 constexpr int kLvMinLog2T4 = 3;
 constexpr int kLvMinWork = 1024;
 constexpr int kLvMinWork4 = 512;
+// The cooperative executors' chunk (level_log2t_barrier): arrivals at the grid
+// barrier that take as long as one more turn.  GRID_BARRIER, int32 SUM, chunks
+// of 4 / 16 / 64 quanta: p = 64, m = 234368, b = 60 (977 quanta a block, 10
+// groups) 1704 / 667 / 611 us; p = 288, m = 26016, b = 60 (108 quanta, 38
+// groups) 550 / 605 / 1253 us; over 200 to 4608 ranks a turn of 8 / 15 / 30
+// arrivals took 0.86 / 0.84 / 0.83 of the time of one chunk per 8192 loads.
+// ROUNDS_BARRIER, whose rounds copy as well and wait longer for their reads:
+// 0.90 / 0.91 / 0.92, and 0.91 / 0.93 / 0.96 without a least chunk.
+constexpr uint64_t kBarrierTurn = 30;
+constexpr uint64_t kRoundsBarrierTurn = 8;
 // From this many ranks (up to 255) level items take one-launch calls of up to
 // one 1 KB chunk of each row per CU (post-order -> level, one fused launch:
 // p = 36, m = 65536 8.9 -> 6.1 us, p = 64 9.5 -> 7.6 us, p = 128 17.0 ->
@@ -962,6 +972,32 @@ int level_log2t(size_t lane_bytes, int p, int g1, const DeviceState& st,
   return lg;
 }
 
+// The same for the cooperative executors, whose rounds end at a grid barrier:
+// every workgroup's arrival there costs, and so does every further turn of
+// leaf groups, `turn` arrivals' worth; chunks of at least 2^least quanta, or
+// what the block holds (items(l): workgroups of a round with 2^l quanta).
+template <class F>
+int level_log2t_barrier(size_t lane_bytes, int g1, const DeviceState& st,
+                        int least, uint64_t turn, F items) {
+  const int forced_lg = env_int("DPAR_LEVEL_LOG2T", -1);
+  int best = 0;
+  uint64_t best_cost = ~0ull;
+  for (int lg = 0; lg <= 6; ++lg) {
+    if (lg > 0 && dpar::level_lds_bytes(lane_bytes, g1, lg) >
+                      (size_t)st.lds_limit - dpar::kStaticLdsReserve)
+      break;
+    const uint64_t turns =
+        (((uint64_t)g1 << lg) + dpar::kLvThreads - 1) / dpar::kLvThreads;
+    const uint64_t cost = items(lg) + turn * turns;
+    if (forced_lg >= 0 ? lg <= forced_lg
+                       : cost < best_cost || (lg <= least && items(lg - 1) > 1)) {
+      best = lg;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 // How work items are evaluated (DPAR_UNIT=seq|level|sub forces one):
 //   SEQ   post-order walk, one wavefront per tree: the default;
 //   LEVEL groups of at most 7 ranks per thread, three tree levels per step
@@ -1091,9 +1127,15 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
         uc.lv_items = lv_items;
         // the chunk itself
         auto count = [&](int l) { return groups * chunks(l); };
-        uc.lv_log2t = one_pass ? flat_lt
-                               : level_log2t(lane_bytes, p, ops.lv.g1, st,
-                                             count);
+        uc.lv_log2t =
+            one_pass ? flat_lt
+            : ex == dpar::Exec::GRID_BARRIER
+                ? level_log2t_barrier(lane_bytes, ops.lv.g1, st, 0,
+                                      kBarrierTurn, count)
+            : ex == dpar::Exec::ROUNDS_BARRIER
+                ? level_log2t_barrier(lane_bytes, ops.lv.g1, st, kLvMinLog2T,
+                                      kRoundsBarrierTurn, count)
+                : level_log2t(lane_bytes, p, ops.lv.g1, st, count);
         uc.lv_C = (int)chunks(uc.lv_log2t);
         return uc;
       }
@@ -1655,10 +1697,14 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
                              dpar::kWideTailChunk);
   }
   // round-structured down-step: two ranks per wavefront per work item, the
-  // largest block in pieces of kDownPiece quanta
+  // largest block in pieces of kDownPiece quanta; level items at a grid
+  // barrier, which every workgroup delays, take twice the ranks (over 7 to
+  // 4608 ranks 0.85 of the time on 64, 0.72 on 288, 0.64 on 4608)
   prm.dslice = 2 * (unit == dpar::Unit::LEVEL ? dpar::kLvThreads / 64
                     : unit == dpar::Unit::SUB ? dpar::kSubParts
                                               : waves);
+  if (unit == dpar::Unit::LEVEL && ex == dpar::Exec::ROUNDS_BARRIER)
+    prm.dslice *= 2;
   {
     const uint64_t maxq = ((s.NL + s.b - 1) / s.b) * (uint64_t)s.lq;
     const uint64_t np = (maxq + dpar::kDownPiece - 1) / dpar::kDownPiece;

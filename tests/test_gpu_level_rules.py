@@ -65,3 +65,21 @@ def test_chunk(p, m, dtype, exec, quanta, capfd):
     need_gpu()
     err = _call(p, m, dtype, exec, 1, 0, capfd)
     assert f" level_chunk_quanta={quanta} " in err, err
+
+
+# the cooperative executors: few workgroups at the barrier, few turns each
+@pytest.mark.parametrize("exec,p,m,b,quanta", [
+    ("barrier", 17, 4 * 705 * 6, 6, 64),
+    ("barrier", 288, 4 * 720 * 6, 6, 16),
+    ("barrier", 1152, 4 * 176 * 6, 6, 4),
+    ("barrier", 4608, 4 * 40 * 3, 3, 1),
+    ("rounds_barrier", 17, 4 * 705 * 6, 6, 64),
+    ("rounds_barrier", 288, 4 * 720 * 6, 6, 32),
+    ("rounds_barrier", 1152, 4 * 176 * 6, 6, 8),
+    ("rounds_barrier", 4608, 4 * 40 * 3, 3, 4),
+    ("rounds_barrier", 2304, 5, 5, 1),
+])
+def test_chunk_at_a_barrier(exec, p, m, b, quanta, capfd):
+    need_gpu()
+    err = _call(p, m, "int32", exec, b, 0, capfd)
+    assert f" level_chunk_quanta={quanta} " in err, err
