@@ -1241,6 +1241,9 @@ void log_plan(int p, size_t m, dpar_dtype_t dtype, dpar_op_t op,
   if (unit == dpar::Unit::WIDE)
     std::fprintf(stderr, " full_items=%u", prm.wide_full);
   if (ex == dpar::Exec::TICKET) std::fprintf(stderr, " batch=%u", prm.batch);
+  if (ex == dpar::Exec::ROUNDS || ex == dpar::Exec::ROUNDS_BARRIER)
+    std::fprintf(stderr, " down_piece=%d down_ranks=%d", prm.dpiece,
+                 prm.dslice);
   if (few) std::fprintf(stderr, " in_registers");
   std::fprintf(stderr, " kernel=%s\n", few ? "few_ranks" : unit_name(run));
 }
@@ -1697,7 +1700,7 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
                              dpar::kWideTailChunk);
   }
   // round-structured down-step: two ranks per wavefront per work item, the
-  // largest block in pieces of kDownPiece quanta; level items at a grid
+  // largest block in pieces of prm.dpiece quanta; level items at a grid
   // barrier, which every workgroup delays, take twice the ranks (over 7 to
   // 4608 ranks 0.85 of the time on 64, 0.72 on 288, 0.64 on 4608)
   prm.dslice = 2 * (unit == dpar::Unit::LEVEL ? dpar::kLvThreads / 64
@@ -1707,7 +1710,9 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
     prm.dslice *= 2;
   {
     const uint64_t maxq = ((s.NL + s.b - 1) / s.b) * (uint64_t)s.lq;
-    const uint64_t np = (maxq + dpar::kDownPiece - 1) / dpar::kDownPiece;
+    prm.dpiece = dpar::down_piece(path, ex == dpar::Exec::ROUNDS_BARRIER, p,
+                                  maxq);
+    const uint64_t np = (maxq + prm.dpiece - 1) / prm.dpiece;
     const uint64_t slices = ((uint64_t)p + prm.dslice - 1) / prm.dslice;
     if (rounds_exec && (uint64_t)prm.C + slices * np >= (1ull << 31))
       return fail(DPAR_ERR_UNSUPPORTED, "more than 2^31 work items per round");

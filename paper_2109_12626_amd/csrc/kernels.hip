@@ -1198,15 +1198,15 @@ __global__ __launch_bounds__(U::kThreads) void k_barrier(DPAR_KARGS) {
 // schedule of Algorithm 1; dshift = b - 1: the broadcast that follows a
 // completed reduction, Section 2's reduce-then-broadcast).
 
-// One rank's share of a down-step piece: up to kDownPiece quanta of the block
-// it receives this round, from its parent's output row to its own (n = 0:
+// One rank's share of a down-step piece: up to PIECE quanta of the block it
+// receives this round, from its parent's output row to its own (n = 0:
 // nothing to receive).
 struct DownPart {
   uint64_t src, dst;  // the piece's first byte in the two rows
   uint32_t par;
   uint32_t n;         // quanta
 };
-template <class L>
+template <class L, int PIECE>
 __device__ __forceinline__ DownPart down_part(const uint64_t* __restrict__ yp,
                                               uint32_t i, uint32_t e,
                                               const Params& prm, int round,
@@ -1216,13 +1216,13 @@ __device__ __forceinline__ DownPart down_part(const uint64_t* __restrict__ yp,
   if (d.par == 0xFFFFFFu || j < 0 || j >= prm.b) return d;  // not in range
   const uint64_t ls = prm.NL * (uint64_t)j / (uint64_t)prm.b;
   const uint64_t le = prm.NL * (uint64_t)(j + 1) / (uint64_t)prm.b;
-  const uint64_t ps = min(ls * prm.lq, prm.Q) + k * kDownPiece;
+  const uint64_t ps = min(ls * prm.lq, prm.Q) + k * PIECE;
   const uint64_t qe = min(le * prm.lq, prm.Q);
   if (ps >= qe) return d;
   const uint64_t off = (prm.qbase + ps) * L::bytes;
   d.src = yp[d.par] + off;
   d.dst = yp[i] + off;
-  d.n = (uint32_t)min((uint64_t)kDownPiece, qe - ps);
+  d.n = (uint32_t)min((uint64_t)PIECE, qe - ps);
   return d;
 }
 
@@ -1234,9 +1234,9 @@ __device__ __forceinline__ void store_kept(uint64_t row, uint32_t off, T v) {
 }
 
 // Down-step for the ranks at positions [a0, a1) of the depth-ordered rank
-// table, piece k (kDownPiece quanta) of their blocks: each wavefront takes two
-// neighbouring ranks, a lane copies kDownPiece / 64 quanta of each, all loads
-// in flight before the stores.
+// table, piece k (PIECE quanta) of their blocks: each wavefront takes two
+// neighbouring ranks, a lane copies PIECE / 64 quanta of each, all loads in
+// flight before the stores.
 //
 // Bound by memory traffic (a rank's block is read from its parent's row and
 // written to its own) and, in short rounds, by the wait on the loads.  Two
@@ -1250,7 +1250,7 @@ __device__ __forceinline__ void store_kept(uint64_t row, uint32_t off, T v) {
 // / 289 / 276 / 268 us; p = 64, m = 1500000, b = 94 901 / 746 / 712 / 680 us;
 // p = 1152, m = 65536 fp32, b = 5 329 / 228 / 214 / 208 us; matrices, p = 120,
 // m = 200001, b = 13 351 / 314 / 309 / 316 us.
-template <class L, int TH>
+template <class L, int TH, int PIECE>
 __device__ __forceinline__ void down_copy(const uint64_t* __restrict__ yp,
                                           const uint32_t* __restrict__ dn,
                                           const uint32_t* __restrict__ ranks,
@@ -1258,14 +1258,14 @@ __device__ __forceinline__ void down_copy(const uint64_t* __restrict__ yp,
                                           uint32_t a0, uint32_t a1,
                                           uint64_t k) {
   constexpr int kWaves = TH / 64;
-  constexpr int kQ = kDownPiece / 64;
+  constexpr int kQ = PIECE / 64;
   const uint32_t lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   for (uint32_t a = a0 + 2 * wave; a < a1; a += 2 * kWaves) {
     const bool two = a + 1 < a1;
     const uint32_t i0 = ranks[a], i1 = ranks[two ? a + 1 : a];
     const uint32_t e0 = dn[i0], e1 = dn[i1];
-    const DownPart d0 = down_part<L>(yp, i0, e0, prm, round, k);
+    const DownPart d0 = down_part<L, PIECE>(yp, i0, e0, prm, round, k);
     if (e1 == e0) {  // siblings (or one rank alone): one parent, one block
       const uint64_t dst1 = yp[i1] + (d0.dst - yp[i0]);
       typename L::T v[kQ];
@@ -1285,7 +1285,7 @@ __device__ __forceinline__ void down_copy(const uint64_t* __restrict__ yp,
       }
       continue;
     }
-    const DownPart d1 = down_part<L>(yp, i1, e1, prm, round, k);
+    const DownPart d1 = down_part<L, PIECE>(yp, i1, e1, prm, round, k);
     typename L::T v[kQ], w[kQ];
 #pragma unroll
     for (int u = 0; u < kQ; ++u) {
@@ -1323,7 +1323,7 @@ __host__ __device__ inline void active_ranks(const uint32_t* doff, int H,
 // Work item `item` of round r: the first C items (r < b) are the up-step's
 // chunks of block r; then, for each slice of dslice active ranks, npieces
 // down-step pieces.
-template <class U>
+template <class U, bool BARRIER>
 __device__ __forceinline__ void round_item(DPAR_KARGS,
                                            const uint32_t* __restrict__ dn,
                                            const uint32_t* __restrict__ ranks,
@@ -1337,8 +1337,18 @@ __device__ __forceinline__ void round_item(DPAR_KARGS,
   const uint64_t d = item - nup;
   const uint32_t a0 = act0 + (uint32_t)(d / (uint64_t)prm.npieces) * prm.dslice;
   const uint32_t a1 = min(act0 + nact, a0 + (uint32_t)prm.dslice);
-  down_copy<typename U::Lane, U::kThreads>(yp, dn, ranks, prm, r, a0, a1,
-                                           d % (uint64_t)prm.npieces);
+  const uint64_t k = d % (uint64_t)prm.npieces;
+  using L = typename U::Lane;
+  // (prm.dpiece, known when the kernel is compiled but in the last case)
+  if constexpr (BARRIER) {
+    down_copy<L, U::kThreads, 2 * kDownPiece>(yp, dn, ranks, prm, r, a0, a1, k);
+  } else if constexpr (L::bytes == 16) {
+    down_copy<L, U::kThreads, kDownPiece>(yp, dn, ranks, prm, r, a0, a1, k);
+  } else if (prm.dpiece == kDownPiece) {
+    down_copy<L, U::kThreads, kDownPiece>(yp, dn, ranks, prm, r, a0, a1, k);
+  } else {
+    down_copy<L, U::kThreads, 2 * kDownPiece>(yp, dn, ranks, prm, r, a0, a1, k);
+  }
 }
 
 template <class U>
@@ -1347,8 +1357,8 @@ __global__ __launch_bounds__(U::kThreads) void k_rounds(
     const uint32_t* __restrict__ dord, int round, uint32_t act0,
     uint32_t nact, uint64_t first) {
   extern __shared__ char lds_raw[];
-  round_item<U>(xp, yp, ops, lvl, prm, dn, dord + prm.dheight + 2, round,
-                act0, nact, first + blockIdx.x, lds_raw);
+  round_item<U, false>(xp, yp, ops, lvl, prm, dn, dord + prm.dheight + 2,
+                       round, act0, nact, first + blockIdx.x, lds_raw);
 }
 
 template <class U>
@@ -1364,8 +1374,8 @@ __global__ __launch_bounds__(U::kThreads) void k_rounds_barrier(
         (r < prm.b ? (uint64_t)prm.C : 0) +
         (uint64_t)((nact + prm.dslice - 1) / prm.dslice) * prm.npieces;
     for (uint64_t it = blockIdx.x; it < items; it += gridDim.x)
-      round_item<U>(xp, yp, ops, lvl, prm, dn, dord + H + 2, r, act0, nact,
-                    it, lds_raw);
+      round_item<U, true>(xp, yp, ops, lvl, prm, dn, dord + H + 2, r, act0,
+                          nact, it, lds_raw);
     if (r + 1 < prm.r1) {
       // the next round reads blocks other workgroups (other XCDs, other L2s)
       // wrote in this one: every wavefront releases its stores at agent
@@ -1788,6 +1798,12 @@ hipError_t launch_few(Kind kind, const FewRun& f, hipStream_t stream) {
     case Kind::MAT: return launch_few_p<LaneMat, 2>(f, stream);
   }
   return hipErrorInvalidValue;
+}
+
+int down_piece(Path path, bool barrier, int p, uint64_t block_quanta) {
+  const bool twice = barrier || (path == Path::SCALAR &&
+                                 (uint64_t)p * block_quanta >= 1u << 21);
+  return twice ? 2 * kDownPiece : kDownPiece;
 }
 
 size_t level_lds_bytes(size_t lane_bytes, int g1, int log2t) {

@@ -78,8 +78,8 @@ struct Params {
                         // (out1 < 0: none)
   int dshift;           // ROUNDS: depth-d rank receives block r - d - dshift
   int dslice;           // ROUNDS: ranks per down-step work item
-  int npieces;          // ROUNDS: down-step pieces per block (kDownPiece
-                        // quanta each)
+  int npieces;          // ROUNDS: down-step pieces per block
+  int dpiece;           // ROUNDS: quanta per piece (down_piece)
   int dheight;          // ROUNDS: height of the real tree(s) (the kernel
                         // form of one tree with p <= 2 is lower)
   int r0, r1;           // ROUNDS: run rounds [r0, r1)
@@ -94,8 +94,9 @@ struct Params {
                         // the full items)
 };
 
-// Quanta per down-step piece: 64 lanes x 2 quanta per lane.
+// Quanta per down-step piece: 64 lanes x 2 quanta per lane, or twice that.
 constexpr int kDownPiece = 128;
+int down_piece(Path path, bool barrier, int p, uint64_t block_quanta);
 
 // Ticket counters per call (each on its own 128-byte line): work-item batch
 // k belongs to counter k % kTicketCounters, which spreads the atomics.

@@ -83,3 +83,22 @@ def test_chunk_at_a_barrier(exec, p, m, b, quanta, capfd):
     need_gpu()
     err = _call(p, m, "int32", exec, b, 0, capfd)
     assert f" level_chunk_quanta={quanta} " in err, err
+
+
+# pieces of 256 quanta at a grid barrier, and with 4-byte lanes from 2^21
+# quanta of all ranks' blocks on; else 128
+@pytest.mark.parametrize("exec,p,m,dtype,b,piece", [
+    ("rounds", 7, 1 << 16, "int32", 4, 128),
+    ("rounds_barrier", 7, 1 << 16, "int32", 4, 256),
+    ("rounds_barrier", 40, 4 * 255 * 3, "int32", 3, 256),
+    ("rounds_barrier", 41, 4 * 257 * 3, "int32", 3, 256),
+    ("rounds_barrier", 41, 513 * 3, "u32mat2x2", 3, 256),
+    ("rounds_barrier", 101, 1027, "float32", 2, 256),
+    ("rounds", 64, 3 * 32767 + 1, "float32", 3, 256),
+    ("rounds", 64, 3 * 32767, "float32", 3, 128),
+    ("rounds", 101, 3 * 20801, "float32", 3, 256),
+])
+def test_down_piece(exec, p, m, dtype, b, piece, capfd):
+    need_gpu()
+    err = _call(p, m, dtype, exec, b, 1, capfd)
+    assert f" down_piece={piece} " in err, err
