@@ -1172,19 +1172,26 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   return uc;
 }
 
-// Threads of a level item in one launch: a thread per quantum of every leaf
-// group, 256 to 1024, while the items have a CU each (they wait on their loads
-// together, so all of them are issued at once).  Several items per CU hide
-// each other's waits and finish more evenly when they are smaller: with 1 KB
-// chunks 512 threads, 256 for few groups (p = 300, m = 100000 fused with 256 /
-// 512 / 1024 threads 40.9 / 45.8 / 43.9 us; p = 1152, m = 131072 split 197 /
-// 188 / 194 us; shorter chunks, p = 2304, m = 131072: 569 / 420 / 377 us).
-int level_threads(int g1, int log2t, uint64_t items, const DeviceState& st) {
+// Threads of a level item that a launch runs `items` of: a thread per quantum
+// of every leaf group, 256 to 1024, while the items have a CU each (they wait on
+// their loads together, so all of them are issued at once).  Several items per
+// CU hide each other's waits and finish more evenly when they are smaller: with
+// 1 KB chunks 256 threads where two workgroups fit a CU by LDS, else 512 (int32
+// SUM, 256 / 512 / 1024 threads, hot: p = 330, m = 90880 fused 39.4 / 48.1 /
+// 43.7 us, p = 511, m = 73376 split 52.8 / 56.8 / 57.1 us, p = 576 (74 groups,
+// 74 KB), m = 75936 split 60.0 / 63.5 / 63.9 us; one per CU, p = 640 (82 groups),
+// m = 68352 81.5 / 71.8 / 70.1 us, p = 1152, m = 131072 197 / 188 / 194 us; shorter
+// chunks, p = 2304, m = 131072 569 / 420 / 377 us).
+int level_threads(size_t lane_bytes, int g1, int log2t, uint64_t items,
+                  const DeviceState& st) {
   const uint64_t cus = (uint64_t)st.num_cus;
   const int work = g1 << log2t;
   int th = 256;
   if (items > cus && log2t == 6)
-    return work <= 2560 ? th : 2 * th;
+    return 2 * dpar::level_lds_bytes(lane_bytes, g1, log2t) <=
+                   (size_t)st.lds_per_cu
+               ? th
+               : 2 * th;
   while (th < dpar::kLvMostThreads && th < work) th *= 2;
   return th;
 }
@@ -1641,7 +1648,11 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
     if (items >= (1ull << 31))
       return fail(DPAR_ERR_UNSUPPORTED, "more than 2^31 work items");
     prm.C = prm.flat ? (int)items : uc.lv_C;
-    prm.lv_threads = level_threads(ops->lv.g1, uc.lv_log2t, items, *st);
+    // (the persistent executors run kLvThreads)
+    if (prm.flat || ex == dpar::Exec::LAUNCH_PER_ROUND)
+      prm.lv_threads = level_threads(
+          path == dpar::Path::VEC16 ? 16 : 4, ops->lv.g1, uc.lv_log2t,
+          prm.flat ? items : (uint64_t)uc.lv_C, *st);
   }
   if (unit == dpar::Unit::SUB) {
     tab.lvl = ops->sub;

@@ -102,3 +102,19 @@ def test_down_piece(exec, p, m, dtype, b, piece, capfd):
     need_gpu()
     err = _call(p, m, dtype, exec, b, 1, capfd)
     assert f" down_piece={piece} " in err, err
+
+
+# more than one 1 KB chunk per CU: 256 threads while two workgroups fit a CU
+# by LDS (80 groups), else 512; launch per round counts one round's items
+@pytest.mark.parametrize("p,m,exec,b,threads", [
+    (300, 65540, "split", 1, 256),
+    (320, 65540, "split", 1, 256),
+    (576, 65540, "split", 1, 256),
+    (640, 65540, "split", 1, 512),
+    (320, 400 * 256, "launch", 8, 1024),
+])
+def test_threads(p, m, exec, b, threads, capfd):
+    need_gpu()
+    err = _call(p, m, "int32", exec, b, 0, capfd)
+    assert f" level_chunk_quanta=64 threads={threads} " in err or \
+        exec == "launch" and f" threads={threads} " in err, err
