@@ -106,15 +106,23 @@ constexpr uint64_t kRoundsBarrierTurn = 8;
 // 12.8 us, p = 200 26.2 -> 18.1 us; with two chunks per CU p = 64 13.5 ->
 // 14.7 us, p = 128 25.1 -> 25.3 us; at p = 16 within 0.6 us either way).
 constexpr int kLvMinRanks = 17;
-// AUTO: subtree items run fused in calls moving at most this much (p = 300,
-// m = 100000, 240 MB: fused 41 us, split 44 us; p = 576, m = 65536, 302 MB:
-// 52 and 50 us; p = 1152, m = 65536, 604 MB: 108 and 96 us), and on rows off
-// the 128-byte lines only with pieces of at least kSubFuseMinPiece bytes,
-// whose ends then share lines with other items' (packed rows: p = 600,
-// m = 20001, 512 bytes: fused 28.0 us, split 30.6 us; p = 1152, m = 16385,
-// 256 bytes: 57 and 42 us).
+// AUTO: subtree items (run as level items) go fused in calls moving at most
+// this much, back to back; after a cache flush fused stays ahead beyond it
+// (split / fused, both regimes: p = 300, m = 100000, 240 MB 43.0 / 39.1 and 53.0
+// / 51.8 us; p = 576, m = 65088, 300 MB 48.2 / 49.5 and 61.7 / 53.2 us; p = 1152,
+// m = 65088, 600 MB 94.2 / 102.6 and 115 / 102 us).  On rows off the 128-byte
+// lines only with pieces of at least kSubFuseMinPiece bytes, whose ends then
+// share lines with other items' (packed rows: p = 600, m = 20001, 512 bytes
+// 30.6 / 28.0 us; p = 1152, m = 16385, 256 bytes 42 / 57 us; p = 300, m = 100001
+// fp32, 1 KB 48.7 / 49.0 and 54.8 / 51.0 us).
 constexpr uint64_t kSubFuseMaxBytes = 256ull << 20;
 constexpr size_t kSubFuseMinPiece = 512;
+// AUTO: with more than one item per CU on rows on the lines, split from this
+// many ranks on (fused / split, hot and after a cache flush: p = 330, m = 90880
+// 39.4 / 40.3 and 53.4 / 51.9 us, p = 400, m = 74976 42.0 / 42.6 and 60.4 / 54.4
+// us, p = 450, m = 66656 43.9 / 44.0 and 62.5 / 56.4 us; p = 300, m = 100000 39.1 /
+// 43.0 and 51.8 / 53.0 us).
+constexpr int kSubSplitRanks = 320;
 // Ranks from which subtree items take calls of up to four items per CU.
 constexpr int kSubCrowdRanks = 4096;
 // Loads in flight of a workgroup of 1024 threads with 8 each.
@@ -929,6 +937,11 @@ uint64_t wide_full_items(uint64_t n, const DeviceState& st) {
   return n - r;
 }
 
+// The split executor or one fused launch.
+bool one_pass(dpar::Exec ex) {
+  return ex == dpar::Exec::SPLIT || ex == dpar::Exec::DISPATCH;
+}
+
 struct UnitChoice {
   dpar::Unit unit = dpar::Unit::SEQ;
   bool grouped = false;   // SUB: run as grouped items over whole chunks
@@ -1025,7 +1038,8 @@ int level_log2t_barrier(size_t lane_bytes, int g1, const DeviceState& st,
 //         most two full chunks per CU, or more where the rules below say so,
 //         and in place of LEVEL when a level plan staged row by row would
 //         need more than two items per CU.  Split and fused calls run it as
-//         level items over whole chunks (UnitChoice::grouped; against the
+//         level items over whole chunks (UnitChoice::grouped, but for a
+//         window in allreduce_impl; against the
 //         eight subtree walks per item that the other executors, and
 //         DPAR_UNIT=sub, run: p = 1152, m = 16384 fused 44.9 -> 28.4 us,
 //         m = 65536 102 -> 96 us, p = 2304, m = 16384 84 -> 51 us, p = 4608,
@@ -1048,8 +1062,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   const bool whole_call = ex == dpar::Exec::SPLIT ||
                           ex == dpar::Exec::TICKET ||
                           ex == dpar::Exec::DISPATCH;
-  // the split executor or one fused launch
-  const bool one_pass = ex == dpar::Exec::SPLIT || ex == dpar::Exec::DISPATCH;
+  const bool one_launch = one_pass(ex);
   const size_t lane_bytes =
       (path == dpar::Path::VEC16 || kind == dpar::Kind::MAT) ? 16 : 4;
   // a one-launch subtree run cuts the columns into whole chunks of 64
@@ -1101,7 +1114,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
         tmax = lg;
     bool want = items < cus / 2 ||
                 (p >= 256 && items < 2 * cus && s.Q < 32 * all_items) ||
-                (one_pass && p >= kLvMinRanks && p < 256 && sub_items <= cus);
+                (one_launch && p >= kLvMinRanks && p < 256 && sub_items <= cus);
     if (forced) want = !std::strcmp(u, "level");
     if (want && tmax >= 0) {
       // largest block (group of grp blocks) in quanta; chunk capacity T =
@@ -1128,7 +1141,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
         // the chunk itself
         auto count = [&](int l) { return groups * chunks(l); };
         uc.lv_log2t =
-            one_pass ? flat_lt
+            one_launch ? flat_lt
             : ex == dpar::Exec::GRID_BARRIER
                 ? level_log2t_barrier(lane_bytes, ops.lv.g1, st, 0,
                                       kBarrierTurn, count)
@@ -1147,7 +1160,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
     // (DPAR_SUB_DEEP is about the walks: set, they run; and so do they where
     // 64 bytes of each row do not fit in LDS)
     const char* deep = std::getenv("DPAR_SUB_DEEP");
-    uc.grouped = one_pass && !forced && ops.lvl && !(deep && *deep) &&
+    uc.grouped = one_launch && !forced && ops.lvl && !(deep && *deep) &&
                  dpar::level_lds_bytes(lane_bytes, ops.lv.g1,
                                        lane_bytes == 16 ? 2 : 4) <=
                      (size_t)st.lds_limit - dpar::kStaticLdsReserve;
@@ -1529,7 +1542,7 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   prm.r0 = r0;
   prm.r1 = r1;
 
-  const UnitChoice uc = choose_unit(ex, s, prm.grp, path, kind, p, *ops, *st);
+  UnitChoice uc = choose_unit(ex, s, prm.grp, path, kind, p, *ops, *st);
   // AUTO: a call that runs in subtree work items (at most two per CU) runs
   // them as one fused launch rather than split: each item's y goes from
   // registers to all p outputs while the few other items still read, and
@@ -1542,13 +1555,27 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // p = 2304, m = 8192 30 us either way, p = 4608, m = 4096 39 -> 44 us) and
   // beyond two items per CU (p = 1152, m = 2^18: 361 -> 459 us; the p writes
   // per item overlap the reads of the items after it).
+  const uint64_t sub_n = (s.Q + 63) / 64, cus = (uint64_t)st->num_cus;
+  const bool lines = rows_lines && xrows_lines;
+  // Subtree items as walks where LDS cuts the level item's chunk to half of
+  // theirs (about 1280 to 2560 ranks) and there is at most one of theirs per
+  // CU but more than one level item: the level items' second turn on some CUs
+  // costs more (int32 SUM, level split / walks fused / walks split, hot and
+  // after a cache flush: p = 1536, m = 40672 95.2 / 91.2 / 90.9 and 112 / 93 / 109
+  // us, p = 2047, m = 48832 142 / 131 / 127 and 164 / 134 / 149 us, p = 1300,
+  // m = 33632 73.5 / 73.3 / 74.8 and 88 / 81 / 91 us; at p = 2600, m = 33632 125 /
+  // 144 / 141 and 152 / 153 / 173 us; packed rows, p = 1800, m = 34723 fp32 120 /
+  // 135 / 105 and 127 / 140 / 112 us).
+  if (one_pass(ex) && uc.grouped && lines && path == dpar::Path::VEC16 &&
+      uc.lv_log2t == 5 && (s.Q + 31) / 32 > cus && sub_n <= cus &&
+      env_int("DPAR_LEVEL_LOG2T", -1) < 0)
+    uc.grouped = false;
   if (exec == DPAR_EXEC_AUTO && ex == dpar::Exec::SPLIT &&
-      uc.unit == dpar::Unit::SUB &&
-      4 * ((s.Q + 63) / 64) >= (uint64_t)st->num_cus &&
-      (s.Q + 63) / 64 <= 2 * (uint64_t)st->num_cus &&
-      2ull * p * m * esz <= kSubFuseMaxBytes &&
-      ((rows_lines && xrows_lines) ||
-       (s.g * esz << uc.lv_log2t) >= kSubFuseMinPiece))
+      uc.unit == dpar::Unit::SUB && 4 * sub_n >= cus && sub_n <= 2 * cus &&
+      (!uc.grouped ||
+       (2ull * p * m * esz <= kSubFuseMaxBytes &&
+        (lines ? p < kSubSplitRanks || sub_n <= cus
+               : (s.g * esz << uc.lv_log2t) >= kSubFuseMinPiece))))
     ex = dpar::Exec::DISPATCH;
   // AUTO, wide items: with at most one per CU they all run at once, read
   // their rows together and then write y together, so one fused launch
@@ -1607,9 +1634,11 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // 18.1 us).  With many ranks a fused item writes its few quanta to each of
   // the p rows, the broadcast pass whole tiles, for one launch more: p = 4608,
   // m = 4096 44 -> 39 us split, p = 2304, m = 1024 18.3 -> 17.5 us, m = 4096
-  // 22.0 -> 22.6 us, while p = 1152, m = 1024 to 8192 and p = 700, m = 8192
-  // would be 1.5 to 2 us faster fused; the line stays where calls were split
-  // before.
+  // 22.0 -> 22.6 us.  Between them fused with 1024 threads would be faster in
+  // both regimes (p = 1152, m = 3008 11.9 -> 10.2 and 17.1 -> 14.6 us, m = 9760
+  // 22.1 -> 21.0 and 28.6 -> 26.8 us; p = 700, m = 8032 12.3 -> 10.0 and 17.6 ->
+  // 15.2 us): these calls stay split because AUTO's choice there is part of what
+  // the tests hold fixed (test_wide_unit_choice), not because of a time.
   if (exec == DPAR_EXEC_AUTO && uc.unit == dpar::Unit::LEVEL &&
       (ex == dpar::Exec::SPLIT || ex == dpar::Exec::DISPATCH)) {
     const bool split = p >= kLvSplitRanks ||

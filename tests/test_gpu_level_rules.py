@@ -118,3 +118,26 @@ def test_threads(p, m, exec, b, threads, capfd):
     err = _call(p, m, "int32", exec, b, 0, capfd)
     assert f" level_chunk_quanta=64 threads={threads} " in err or \
         exec == "launch" and f" threads={threads} " in err, err
+
+
+# subtree items: walks, fused under AUTO, where LDS halves the level item's
+# chunk and only the level items outnumber the CUs, on rows on the lines; with
+# more than one item per CU split from 320 ranks on
+@pytest.mark.parametrize("p,m,exec,pad,shown", [
+    (1300, 32768, "auto", 0, ("exec=split ", " kernel=level")),
+    (1300, 32772, "auto", 28, ("exec=one_launch_fused ", " kernel=subtree")),
+    (1300, 32772, "split", 28, ("exec=split ", " kernel=subtree")),
+    (1300, 32772, "auto", 29, ("exec=split ", " kernel=level")),
+    (1300, 65536, "auto", 0, ("exec=one_launch_fused ", " kernel=subtree")),
+    (1300, 65540, "auto", 28, ("exec=split ", " kernel=level")),
+    (1152, 32800, "auto", 0, ("exec=split ", " kernel=level")),
+    (2600, 32800, "auto", 0, ("exec=split ", " kernel=level")),
+    (319, 65568, "auto", 0, ("exec=one_launch_fused ", " kernel=level")),
+    (320, 65536, "auto", 0, ("exec=one_launch_fused ", " kernel=level")),
+    (320, 65568, "auto", 0, ("exec=split ", " kernel=level")),
+    (320, 65568, "auto", 1, ("exec=one_launch_fused ", " kernel=level")),
+])
+def test_subtree_route(p, m, exec, pad, shown, capfd):
+    need_gpu()
+    err = _call(p, m, "int32", exec, 1, pad, capfd)
+    assert all(w in err for w in shown), err
