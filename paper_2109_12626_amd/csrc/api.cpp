@@ -954,16 +954,28 @@ struct UnitChoice {
 // CU, from the few quanta that the constants above say to what fits in LDS, at
 // most 64 (items(l): how many items there are with 2^l quanta).  With 16-byte
 // lanes four quanta also while there are more items than an eighth of the
-// CUs, and from kLvCrowdRanks ranks on whole lines once items for half the CUs
-// remain (p = 4608, m = 4000 in chunks of 4 / 8 / 16 quanta 41.6 / 35.2 / 50.9
-// us, p = 2304, m = 8192 45.4 / 30.4 / 35.5 us; p = 1152, m = 4000 13.7 / 14.1 /
-// 17.9 us).  Pieces of less than 64 bytes (4-byte lanes) share their lines with
-// more items, so those grow from 5/8 of an item per CU on (p = 700, m = 1001,
-// 251 items of 4 quanta 11.1 us, 126 of 8 9.2 us; p = 1152, m = 513, 129 items
-// of 4 quanta 10.0 us, 65 of 8 11.1 us).  DPAR_LEVEL_LOG2T forces it.
+// CUs, and from kLvCrowdRanks ranks on whole lines with items for half the CUs
+// (p = 4608, m = 4000 in chunks of 4 / 8 / 16 quanta 41.6 / 35.2 / 50.9 us,
+// p = 2304, m = 8192 45.4 / 30.4 / 35.5 us; p = 1152, m = 4000 13.7 / 14.1 / 17.9
+// us; packed rows, p = 4608, m = 813 47 / 56 us), or an eighth where LDS holds no
+// more than a line (p = 6000, m = 625 66.6 / 52.9 us).  4-byte lanes: 16-byte
+// pieces share their lines with seven others, so they grow from 5/8 of an
+// item per CU on (p = 700, m = 1001, 251 items of 4 quanta 11.1 us, 126 of 8 9.1
+// us; p = 1152, m = 513, 129 items of 4 quanta 10.0 us, 65 of 8 11.1 us; single
+// quanta not: p = 4608, m = 251 20.8 us, in pairs 21.9 us), 32-byte
+// ones while a longer chunk costs no turn or every item writes all rows (251
+// items of 8 quanta / 126 of 16, p = 288, m = 2001 7.2 / 6.7 us, launch per
+// round p = 1152 20.2 / 18.8 us; p = 1152, AUTO 16.3 / 17.8 us); and in ROUNDS,
+// whose down-step items fill the CUs as well, 64-byte ones of more than one
+// turn from two per CU on (chunks of 16 / 32 quanta, b = 5: p = 1152, 6511
+// quanta a block 232 / 254 us, p = 4608 766 / 905 us; with fewer places p = 288,
+// 5000 quanta, b = 1 50 / 38 us).  A
+// ticket costs a claim per item, so there they start longer (4 to 8 / 16
+// quanta, p = 320, m = 1563 15.7 / 10.3 us, p = 1152, m = 435 17.5 / 15.4 us).
+// DPAR_LEVEL_LOG2T forces it.
 template <class F>
 int level_log2t(size_t lane_bytes, int p, int g1, const DeviceState& st,
-                F items) {
+                dpar::Exec ex, F items) {
   int top = 6;
   while (top > 0 && dpar::level_lds_bytes(lane_bytes, g1, top) >
                         (size_t)st.lds_limit - dpar::kStaticLdsReserve)
@@ -972,16 +984,31 @@ int level_log2t(size_t lane_bytes, int p, int g1, const DeviceState& st,
   if (forced_lg >= 0) return std::min(forced_lg, top);
   const uint64_t cus = (uint64_t)st.num_cus;
   const bool wide = lane_bytes == 16;
-  int lg = std::min(top, wide ? kLvMinLog2T : kLvMinLog2T4);
+  const bool ticket4 = ex == dpar::Exec::TICKET && !wide;
+  int lg = std::min(top, wide      ? kLvMinLog2T
+                         : ticket4 ? kLvMinLog2T4 + 1
+                                   : kLvMinLog2T4);
   const int least = lg;
-  while (lg > 0 && g1 << lg > (wide ? kLvMinWork : kLvMinWork4)) --lg;
+  const int work = wide ? kLvMinWork : ticket4 ? 5 * kLvMinWork4 : kLvMinWork4;
+  while (lg > 0 && g1 << lg > work) --lg;
   if (wide) {
     while (lg < least && 8 * items(lg) > cus) ++lg;
-    if (p >= kLvCrowdRanks && lg < top && 2 * items(lg) >= cus) ++lg;
+    if (p >= kLvCrowdRanks && lg < top &&
+        (top == 3 ? 8 : 2) * items(lg) >= cus)
+      ++lg;
   }
-  while (lg < top &&
-         items(lg) > ((lane_bytes << lg) < 64 ? 5 * cus / 8 : cus))
-    ++lg;
+  auto most = [&](int l) {
+    const size_t piece = lane_bytes << l;
+    if (l > 0 && piece < 64 &&
+        (piece < 32 || ex == dpar::Exec::LAUNCH_PER_ROUND ||
+         g1 << l < kLvMinWork4))
+      return 5 * cus / 8;
+    return ex == dpar::Exec::ROUNDS && !wide && piece >= 64 &&
+                   g1 << l >= kLvMinWork
+               ? 2 * cus
+               : cus;
+  };
+  while (lg < top && items(lg) > most(lg)) ++lg;
   return lg;
 }
 
@@ -1091,7 +1118,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
                          sub_items <= 4 * cus;
   // chunk of a level item that follows no blocks
   const int flat_lt =
-      ops.lvl ? level_log2t(lane_bytes, p, ops.lv.g1, st,
+      ops.lvl ? level_log2t(lane_bytes, p, ops.lv.g1, st, ex,
                             [&](int l) { return (s.Q + (1ull << l) - 1) >> l; })
               : 0;
   bool want_sub = p >= 256 && sub_fits &&
@@ -1148,7 +1175,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
             : ex == dpar::Exec::ROUNDS_BARRIER
                 ? level_log2t_barrier(lane_bytes, ops.lv.g1, st, kLvMinLog2T,
                                       kRoundsBarrierTurn, count)
-                : level_log2t(lane_bytes, p, ops.lv.g1, st, count);
+                : level_log2t(lane_bytes, p, ops.lv.g1, st, ex, count);
         uc.lv_C = (int)chunks(uc.lv_log2t);
         return uc;
       }

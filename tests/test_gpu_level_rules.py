@@ -49,17 +49,27 @@ def _call(p, m, dtype, exec, b, pad, capfd):
     (288, 1, "float32", "auto", 8),
     (1152, 33, "int32", "auto", 2),
     (4608, 7, "float32", "auto", 1),
-    (4608, 161, "float32", "auto", 2),
+    (4608, 255, "float32", "auto", 1),
+    (4608, 257, "float32", "auto", 2),
     (6000, 5, "float32", "split", 1),
     (4608, 3, "u32mat2x2", "auto", 1),
     (4608, 33, "u32mat2x2", "auto", 2),
     (4608, 65, "u32mat2x2", "auto", 4),
     (2304, 512, "u32mat2x2", "auto", 8),
     (2304, 508, "u32mat2x2", "auto", 4),
+    (6000, 128, "u32mat2x2", "auto", 8),
+    (6000, 124, "u32mat2x2", "auto", 4),
+    (288, 2001, "float32", "auto", 16),
+    (1152, 1301, "float32", "launch", 16),
+    (1152, 2049, "float32", "auto", 16),
+    (1152, 2045, "float32", "auto", 8),
+    (1152, 5615, "float32", "rounds", 16),
+    (288, 5615, "float32", "rounds", 32),
     (1152, 1024, "u32mat2x2", "auto", 4),
     (4608, 27, "u32mat2x2", "launch", 1),
     (2304, 217, "float32", "rounds", 2),
-    (2304, 13, "int32", "ticket", 1),
+    (2304, 13, "int32", "ticket", 8),
+    (320, 1563, "float32", "ticket", 16),
 ])
 def test_chunk(p, m, dtype, exec, quanta, capfd):
     need_gpu()
