@@ -1169,7 +1169,7 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
         auto count = [&](int l) { return groups * chunks(l); };
         uc.lv_log2t =
             one_launch ? flat_lt
-            : ex == dpar::Exec::GRID_BARRIER
+            : ex == dpar::Exec::GRID_BARRIER && s.b > 1
                 ? level_log2t_barrier(lane_bytes, ops.lv.g1, st, 0,
                                       kBarrierTurn, count)
             : ex == dpar::Exec::ROUNDS_BARRIER
@@ -1767,18 +1767,21 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
                              dpar::kWideTailChunk);
   }
   // round-structured down-step: two ranks per wavefront per work item, the
-  // largest block in pieces of prm.dpiece quanta; level items at a grid
-  // barrier, which every workgroup delays, take twice the ranks (over 7 to
-  // 4608 ranks 0.85 of the time on 64, 0.72 on 288, 0.64 on 4608)
+  // largest block in pieces of prm.dpiece quanta
   prm.dslice = 2 * (unit == dpar::Unit::LEVEL ? dpar::kLvThreads / 64
                     : unit == dpar::Unit::SUB ? dpar::kSubParts
                                               : waves);
-  if (unit == dpar::Unit::LEVEL && ex == dpar::Exec::ROUNDS_BARRIER)
-    prm.dslice *= 2;
   {
     const uint64_t maxq = ((s.NL + s.b - 1) / s.b) * (uint64_t)s.lq;
     prm.dpiece = dpar::down_piece(path, ex == dpar::Exec::ROUNDS_BARRIER, p,
                                   maxq);
+    // level items at a grid barrier, which every workgroup delays, take twice
+    // the ranks, or four times from 2^18 quanta of all ranks' blocks on (16 /
+    // 32 / 64 ranks, int32 SUM, b = 60: p = 64, 977 quanta a block 817 / 776 /
+    // 1059 us, p = 288, 723 quanta 1817 / 1368 / 1361 us; b = 16: p = 512, 1525
+    // quanta 1714 / 1169 / 862 us; b = 5: p = 64, 5859 quanta 464 / 333 / 277 us)
+    if (unit == dpar::Unit::LEVEL && ex == dpar::Exec::ROUNDS_BARRIER)
+      prm.dslice *= (uint64_t)p * maxq >= 1u << 18 ? 4 : 2;
     const uint64_t np = (maxq + prm.dpiece - 1) / prm.dpiece;
     const uint64_t slices = ((uint64_t)p + prm.dslice - 1) / prm.dslice;
     if (rounds_exec && (uint64_t)prm.C + slices * np >= (1ull << 31))

@@ -83,6 +83,7 @@ def test_chunk(p, m, dtype, exec, quanta, capfd):
     ("barrier", 288, 4 * 720 * 6, 6, 16),
     ("barrier", 1152, 4 * 176 * 6, 6, 4),
     ("barrier", 4608, 4 * 40 * 3, 3, 1),
+    ("barrier", 1152, 6496, 1, 8),
     ("rounds_barrier", 17, 4 * 705 * 6, 6, 64),
     ("rounds_barrier", 288, 4 * 720 * 6, 6, 32),
     ("rounds_barrier", 1152, 4 * 176 * 6, 6, 8),
@@ -112,6 +113,19 @@ def test_down_piece(exec, p, m, dtype, b, piece, capfd):
     need_gpu()
     err = _call(p, m, dtype, exec, b, 1, capfd)
     assert f" down_piece={piece} " in err, err
+
+
+# ranks per down-step item at a barrier: 32, 64 from 2^18 quanta of all ranks'
+# blocks on (lines of 8 quanta)
+@pytest.mark.parametrize("exec,p,m,ranks", [
+    ("rounds", 64, 4 * 4096 * 2, 16),
+    ("rounds_barrier", 64, 4 * 4088 * 2, 32),
+    ("rounds_barrier", 64, 4 * 4096 * 2, 64),
+])
+def test_down_ranks(exec, p, m, ranks, capfd):
+    need_gpu()
+    err = _call(p, m, "int32", exec, 2, 0, capfd)
+    assert f" down_ranks={ranks} " in err, err
 
 
 # more than one 1 KB chunk per CU: 256 threads while two workgroups fit a CU
