@@ -1832,9 +1832,30 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
   // and 11.5 us; rows of 32 MB: p = 8 96.6 and 95.4 us, p = 3 35.1 and
   // 34.4 us; of 64 MB: p = 4 93.6 and 90.8 us, p = 2 45.6 and 44.3 us).  A
   // work item that a switch picks or shapes is run as asked.
+  // Two exceptions.  Its workgroups take 512 quanta, so a little more than one
+  // per CU leaves CUs idle: from 5 ranks on (8 in place) post-order items in
+  // full chunks are faster there, from 8 of them per CU to 13, where no
+  // trailing elements ask for a launch of their own (back to back, few /
+  // post-order: p = 5, m = 557056 5.4 / 5.0 us; p = 6, m = 655360 7.0 / 5.7 us; p
+  // = 8, m = 786432 9.0 / 7.8 us; chunks of a third of a block, p = 6,
+  // m = 720896 7.0 / 7.3 us, p = 8, m = 819200 9.0 / 10.5 us; with b = 1 0.76 to
+  // 0.95 of the time all along; p = 4 0.91 to 1.05; in place p = 5 1.2 to 1.6,
+  // p = 8 0.83 to 0.92; after a cache flush within 6% either way).  And on
+  // long rows off the 128-byte lines, 3 to 6 ranks (rows of 32 to 128 MB fp32,
+  // few over wide, 16 bytes past a line: p = 2 1.02, p = 3 1.04, p = 4 1.04, p = 5
+  // 1.05, p = 6 1.05, p = 7 0.99; packed rows of 4 k + 1 elements 0.94 / 0.97 /
+  // 0.99 / 1.01 / 1.01 / 0.96, at 94 MB p = 5 1.05).
+  const uint64_t post = (s.Q + 63) / 64;
+  const bool post_order = unit == dpar::Unit::SEQ && s.tail == 0 &&
+                          p >= (x[0] == y[0] ? 8 : 5) && post > 8 * ncu &&
+                          post <= 13 * ncu &&
+                          4 * grouped_units(s, prm.grp) <= 5 * post;
+  const bool lines_only = p >= 3 && p <= 6 && (s.tail == 0 || p >= 5);
   const bool few = exec == DPAR_EXEC_AUTO && up == dpar::Exec::DISPATCH &&
                    p <= dpar::kFewRanks && path == dpar::Path::VEC16 &&
-                   (wide_n <= ncu || (uint64_t)m * esz >= kFewRowBytes) &&
+                   (wide_n <= ncu ? !post_order
+                                  : (uint64_t)m * esz >= kFewRowBytes &&
+                                        (lines || !lines_only)) &&
                    !item_switch_set();
   // (its trailing elements are its own: not the level item's)
   if (few) tail = s.tail;

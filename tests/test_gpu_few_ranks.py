@@ -91,3 +91,46 @@ def test_rule_edges(p, m, few, capfd):
     err = capfd.readouterr().err
     assert ("in_registers" in err) == few, err
     assert bool((y == x.sum(0, dtype=torch.int64).to(torch.int32)).all())
+
+
+# a little more than one of its workgroups per CU: post-order items in full
+# chunks from 5 ranks on (8 in place), 8 to 13 of them per CU, without trailing
+# elements; long rows off the 128-byte lines: wide items with 3 to 6 ranks
+@pytest.mark.parametrize("p,m,off,kernel", [
+    (4, (1 << 19) + 4, 0, "few_ranks"),
+    (5, 1 << 19, 0, "few_ranks"),
+    (5, (1 << 19) + 4, 0, "postorder"),
+    (5, 9 << 16, 0, "postorder"),
+    (5, 608 << 10, 0, "few_ranks"),        # three chunks a block
+    (8, 12 << 16, 3, "postorder"),
+    (8, 800 << 10, 0, "few_ranks"),
+    (8, (12 << 16) - 1, 0, "few_ranks"),
+    (7, 9 << 16, None, "few_ranks"),       # in place
+    (8, 9 << 16, None, "postorder"),
+    (2, 1 << 23, 1, "few_ranks"),
+    (3, 1 << 23, 0, "few_ranks"),
+    (3, 1 << 23, 4, "wide"),
+    (6, 1 << 23, 1, "wide"),
+    (4, (1 << 23) + 2, 1, "few_ranks"),
+    (6, (1 << 23) + 2, 1, "wide"),
+    (7, 1 << 23, 1, "few_ranks"),
+])
+def test_rule_exceptions(p, m, off, kernel, capfd):
+    need_gpu()
+    dpar = lib()
+    in_place, off = off is None, off or 0
+    ld = -(-m // 32) * 32 + 32
+    x = torch.randint(-1000, 1000, (p, ld), dtype=torch.int32, device="cuda")
+    x[:, :off] = 0
+    x[:, off + m:] = 0
+    want = x[:, off:off + m].sum(0, dtype=torch.int64).to(torch.int32)
+    y = x if in_place else torch.zeros_like(x)
+    s = torch.cuda.current_stream()
+    with env_unit(None), _Env("DPAR_LOG", 1):
+        dpar.dpar_allreduce(dpar.rows(x[:, off:]), dpar.rows(y[:, off:]), p,
+                            m, "int32", "sum", 0, s)
+    dpar.dpar_check_status(s)
+    err = capfd.readouterr().err
+    assert f" kernel={kernel}\n" in err, err
+    assert bool((y[:, off:off + m] == want).all())
+    assert bool((y[:, :off] == 0).all() and (y[:, off + m:] == 0).all())
