@@ -95,24 +95,33 @@ typedef enum {
  *                     streams y_0 into the other p - 1 outputs.  HBM reads
  *                     and writes share one bus, so separating the two
  *                     directions avoids read/write turnarounds.
- *   AUTO              SPLIT; one launch of every work item in round order
- *                     with the fused write-out instead for calls moving at
- *                     most 40 MB (2 p m times the element size) unless they
- *                     run in level work items with p >= 1024, for calls
- *                     that run in level work items below that, for calls
- *                     that
- *                     run in post-order work items on rows of at most
- *                     3.5 MB (p <= 16), 2.5 MB (p <= 48), 1.5 MB (p <= 64),
- *                     1 MB (p <= 96) or 512 KB,
- *                     for calls that run in subtree work items (p >= 256
- *                     and at most two such items per CU, at least one per
- *                     four CUs) and move at most 256 MB (on rows off the
- *                     128-byte lines only in pieces of at least 512 bytes;
- *                     other such calls run split), and for calls that run in
- *                     wide work items
- *                     with p <= 36 and at most one such item (16 KB of
- *                     columns) per CU, with p <= 20 and at most two, or
- *                     with p <= 8.
+ *   AUTO              SPLIT, or one launch of every work item in round order
+ *                     with the fused write-out
+ *                     - for calls moving at most 40 MB (2 p m times the
+ *                       element size) unless they run in level work items
+ *                       with p >= 1024, or with p >= 512 and one per CU;
+ *                     - for calls that run in level work items below that:
+ *                       few or short blocks, and with p = 17 .. 255 every
+ *                       call of at most one chunk of 64 quanta per CU;
+ *                     - for calls that run in post-order work items on rows
+ *                       of at most 3.5 MB (p <= 16), 2.5 MB (p <= 48),
+ *                       1.5 MB (p <= 64), 1 MB (p <= 96) or 512 KB;
+ *                     - for calls that run in subtree work items (p >= 256
+ *                       and at most two such items, chunks of 64 quanta, per
+ *                       CU, at least one per four CUs) and move at most
+ *                       256 MB, on rows off the 128-byte lines only in pieces
+ *                       of at least 512 bytes, on rows on them from p = 320 on
+ *                       only with at most one item per CU; and, whatever they
+ *                       move, for those of about 1280 to 2560 ranks on rows on
+ *                       the lines with more than half an item and at most
+ *                       one per CU;
+ *                     - for calls that run in wide work items with p <= 36
+ *                       and at most one such item (16 KB of columns) per CU,
+ *                       with p <= 20 and at most two, or with p <= 8.
+ *                     One such launch of at most 8 ranks on 16-byte lanes, on
+ *                     rows of at most 4 MB or of 32 MB and more, keeps all
+ *                     rows in registers, but for two windows where the
+ *                     post-order or wide items are faster.
  * The last two run the algorithm's whole round structure, down-phase
  * included (dpar_schedule_rounds gives the number of rounds R):
  *   ROUNDS            one launch per round r = 0 .. R-1.  Round r runs the
@@ -127,8 +136,8 @@ typedef enum {
  *                     the root, b + j + d_i - 1 otherwise).
  *   ROUNDS_BARRIER    the same rounds in one persistent (co-resident) launch
  *                     with a device-wide barrier between rounds.
- * These two read each rank's block from its parent's output, so their HBM
- * traffic is about 1.5 times the others'.
+ * These two read each block from the parent's output, once for two children,
+ * so their HBM traffic is about 1.25 times the others'.
  * Every wait at a device-wide barrier is bounded (DPAR_SPIN_LIMIT polls).  A
  * wait that gives up ends the waiting of the rest of that call (its later
  * barriers pass at once), sets a device-wide report flag that
@@ -340,7 +349,9 @@ int dpar_set_phase_event(hipEvent_t ev);
 const char* dpar_last_error(void);
 
 /* Tuning and test knobs, read from the environment at every call; none of
- * them changes what a call computes:
+ * them changes what a call computes.  With DPAR_UNIT, DPAR_WAVES,
+ * DPAR_WIDE_TAIL, DPAR_WIDE_ROUND or DPAR_LEVEL_LOG2T set, calls of at most 8
+ * ranks run the work item the knob is about, not the register kernel:
  *   DPAR_UNIT=seq|level|sub|wide
  *                           force the post-order, level, subtree or wide
  *                           post-order work item (wide: 16-byte lanes and
@@ -375,10 +386,12 @@ const char* dpar_last_error(void);
  *   DPAR_SPLIT_UP=ticket    SPLIT's up-phase on the ticketed persistent
  *                           kernel instead of one launch (comparison)
  *   DPAR_FUSE_BELOW_KB=n    AUTO's single-launch threshold (default 40960)
- *   DPAR_GROUP_BLOCKS=0     one-launch executors (SPLIT, TICKET, AUTO):
+ *   DPAR_GROUP_BLOCKS=0     one-launch executors (SPLIT, TICKET, AUTO),
+ *                           post-order work items and TICKET's level items:
  *                           one work item per block even when blocks are
  *                           shorter than half a chunk (default 1: groups of
- *                           consecutive whole blocks)
+ *                           consecutive whole blocks; the other items of
+ *                           these executors follow no blocks)
  *   DPAR_SCALAR=1           one element per lane and the canonical
  *                           element partition for INT32/FLOAT32 (tests)
  *   DPAR_BCAST_SPAN_KB=n    SPLIT's broadcast pass: y_0 streamed out in

@@ -1127,13 +1127,18 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
   if (ops.lvl) {
     // Level or subtree.  In one launch both run the same item and the family
     // only sets who writes the outputs (the AUTO rules in allreduce_impl);
-    // with the ticket executor subtree items are walks, which are the better
-    // ones when level items would be many and hold little of each row.  The
-    // measure is the chunk that fits when a level item stages its quanta of
-    // all p rows in LDS, with its loads in flight at once, larger only while
-    // such items outnumber the CUs: more than two per CU (four from
-    // kLvCrowdRanks ranks on) are too many, and so is more than one if there
-    // are subtree items for a quarter of the CUs.
+    // with the ticket executor subtree items are walks.  The measure is not the
+    // present item's: it counts the items of one that stages its quanta of
+    // all p rows in LDS with its loads in flight at once, longer only while
+    // they outnumber the CUs, and calls more than two per CU (four from
+    // kLvCrowdRanks ranks on) too many, and more than one if there are subtree
+    // items for a quarter of the CUs.  In one launch the line is where it
+    // should be or costs little (int32 SUM, the executor of its side / of the
+    // other, back to back: p = 400, m = 14048 level, fused 10.0 / split 12.2 us,
+    // m = 18720 subtree, fused 14.6 / 16.3; p = 1152, m = 12992 split 24.9 / fused
+    // 23.4, m = 17344 fused 33.4 / split 35.6; p = 2304, m = 4864 level, split 24.2
+    // / fused 23.2, m = 8672 subtree, split 35.0 / fused 34.1), and the tests hold
+    // AUTO's choice on both sides of it fixed (test_wide_unit_choice).
     int tmax = -1;
     for (int lg = 6; lg >= 0 && tmax < 0; --lg)
       if ((((uint64_t)p + 1) << lg) * lane_bytes + 12ull * (uint64_t)p + 256 <=
@@ -1142,7 +1147,12 @@ UnitChoice choose_unit(dpar::Exec ex, const dpar::Schedule& s, int grp,
     bool want = items < cus / 2 ||
                 (p >= 256 && items < 2 * cus && s.Q < 32 * all_items) ||
                 (one_launch && p >= kLvMinRanks && p < 256 && sub_items <= cus);
-    if (forced) want = !std::strcmp(u, "level");
+    if (forced) {
+      want = !std::strcmp(u, "level");
+      if (tmax < 0 && dpar::level_lds_bytes(lane_bytes, ops.lv.g1, 0) <=
+                          (size_t)st.lds_limit - dpar::kStaticLdsReserve)
+        tmax = 0;  // (the rule's measure, not the item's own)
+    }
     if (want && tmax >= 0) {
       // largest block (group of grp blocks) in quanta; chunk capacity T =
       // a power of two
@@ -1900,7 +1910,7 @@ int allreduce_impl(const void* const* x, void* const* y, int p, size_t m,
     tp.grp = 1;
     tp.batch = 1;
     tp.xcd_runs = 0;
-    // at most 3 elements: evaluated level by level (all p loads at once)
+    // at most 3 elements: a level item (all p loads at once)
     // where the group table exists; a post-order walk would be a chain of
     // p / 2 dependent loads (p = 288, 2125 elements: 47 us per call with
     // the walk)

@@ -19,13 +19,13 @@
 //     passes it from parent to child one depth per round.
 //
 // Short chunks can instead be evaluated in groups of at most 7 ranks per
-// thread, three tree levels per step (run_unit_lv).  Round sequencing: all work items in round order in
-// one launch (split: the hardware dispatcher hands them out), one launch per
-// round, a persistent kernel with a grid barrier per round, a persistent
-// kernel that claims work items from atomic tickets in round order, or the
-// full round structure including the down-phase (k_rounds,
-// k_rounds_barrier).  One tree (Sections 1.2, 2) runs through the same code
-// in a two-part form (plan.hpp kernel_single_tree).
+// thread, three tree levels per step (run_unit_lv).  Round sequencing: all
+// work items in round order in one launch (split: the hardware dispatcher
+// hands them out), one launch per round, a persistent kernel with a grid
+// barrier per round, a persistent kernel that claims work items from atomic
+// tickets in round order, or the full round structure including the
+// down-phase (k_rounds, k_rounds_barrier).  One tree (Sections 1.2, 2) runs
+// through the same code in a two-part form (plan.hpp kernel_single_tree).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -1241,15 +1241,20 @@ __device__ __forceinline__ void store_kept(uint64_t row, uint32_t off, T v) {
 // Bound by memory traffic (a rank's block is read from its parent's row and
 // written to its own) and, in short rounds, by the wait on the loads.  Two
 // children of one parent are neighbours in the table and receive the same
-// block in the same round: it is read once and written twice.  The stores are
-// ordinary ones, unlike the other kernels': the next round reads what they
-// write.  Pieces of 128 quanta leave twice the wavefronts of 256 to overlap
-// with the round's up-step; 64 gain nothing more.  int32 SUM, one MI355X, one
-// launch per round, each rank on its own with a streaming store / shared reads
-// / ordinary stores as well / with 128 quanta: p = 288, m = 250000, b = 16 321
-// / 289 / 276 / 268 us; p = 64, m = 1500000, b = 94 901 / 746 / 712 / 680 us;
-// p = 1152, m = 65536 fp32, b = 5 329 / 228 / 214 / 208 us; matrices, p = 120,
-// m = 200001, b = 13 351 / 314 / 309 / 316 us.
+// block in the same round: it is read once and written twice.  (Where tree A
+// has an odd number of ranks on its last level, tree B's pairs there are split
+// between wavefronts and read on their own.)  The stores are ordinary ones,
+// unlike the other kernels': the next round reads what they write.
+//
+// Pieces of 128 quanta leave twice the wavefronts of 256 to overlap with the
+// round's up-step; 64 gain nothing more.  At a grid barrier, which every
+// workgroup delays, and with 4-byte lanes in long rounds pieces of 256 are
+// faster (down_piece).  int32 SUM, one MI355X, one launch per round, each rank
+// on its own with a streaming store / shared reads / ordinary stores as well /
+// with 128 quanta: p = 288, m = 250000, b = 16 321 / 289 / 276 / 268 us; p = 64,
+// m = 1500000, b = 94 901 / 746 / 712 / 680 us; p = 1152, m = 65536 fp32, b = 5
+// 329 / 228 / 214 / 208 us; matrices, p = 120, m = 200001, b = 13, the one that
+// lost by the last step, 351 / 314 / 309 / 316 us.
 template <class L, int TH, int PIECE>
 __device__ __forceinline__ void down_copy(const uint64_t* __restrict__ yp,
                                           const uint32_t* __restrict__ dn,
@@ -1800,6 +1805,13 @@ hipError_t launch_few(Kind kind, const FewRun& f, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
+// ROUNDS_BARRIER, int32 SUM, pieces of 128 / 256 quanta (16 ranks an item): p =
+// 64, m = 781248, b = 60 2773 / 1769 us, p = 288, m = 173600, b = 60 2989 / 1918 us,
+// p = 512, m = 14624, b = 5 747 / 469 us.  ROUNDS with 4-byte lanes, fp32, 400 MB,
+// b = 5: p = 7 211 / 198 us, p = 64 197 / 174 us, p = 288 258 / 234 us; of 2^21
+// quanta of all ranks' blocks and fewer 128 are as fast or faster (p = 64, 23437
+// quanta a block 1.02 of the time with 256, 46875 0.95; p = 1152 1302 1.03, 2604
+// 0.96; p = 7, m = 71429 1.25).
 int down_piece(Path path, bool barrier, int p, uint64_t block_quanta) {
   const bool twice = barrier || (path == Path::SCALAR &&
                                  (uint64_t)p * block_quanta >= 1u << 21);

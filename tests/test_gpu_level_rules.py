@@ -67,7 +67,8 @@ def _call(p, m, dtype, exec, b, pad, capfd):
     (288, 5615, "float32", "rounds", 32),
     (1152, 1024, "u32mat2x2", "auto", 4),
     (4608, 27, "u32mat2x2", "launch", 1),
-    (2304, 217, "float32", "rounds", 2),
+    (2304, 217, "float32", "rounds", 1),
+    (2304, 257, "float32", "rounds", 2),
     (2304, 13, "int32", "ticket", 8),
     (320, 1563, "float32", "ticket", 16),
 ])

@@ -32,3 +32,21 @@ def test_switch_reaches_its_call(p, m, name, value, shown, capfd):
     err = capfd.readouterr().err
     assert shown in err and "in_registers" not in err, err
     assert bool((y == x.sum(0, dtype=torch.int64).to(torch.int32)).all())
+
+
+@pytest.mark.parametrize("p", [6000, 12000])
+@pytest.mark.parametrize("exec", ["auto", "split", "launch", "rounds"])
+def test_level_item_wherever_its_chunk_fits(p, exec, capfd):
+    """A level item needs LDS for p / 8 values, not for p rows."""
+    need_gpu()
+    dpar = lib()
+    x = torch.randint(-1000, 1000, (p, 520), dtype=torch.int32, device="cuda")
+    y = torch.zeros_like(x)
+    s = torch.cuda.current_stream()
+    with env_unit("level"), _Env("DPAR_LOG", 1):
+        dpar.dpar_allreduce_ex(dpar.rows(x), dpar.rows(y), p, 520, "int32",
+                               "sum", 2, exec, s)
+    dpar.dpar_check_status(s)
+    err = capfd.readouterr().err
+    assert "unit=level " in err and " kernel=level\n" in err, err
+    assert bool((y == x.sum(0, dtype=torch.int64).to(torch.int32)).all())
